@@ -22,13 +22,15 @@
 // clean vertex, the first vertex that is not final would be pending with its
 // final, clean key. The tree stops there; every clean key is then final.
 //
-// Dedup of the lists uses 4 bits per vertex in a flag word array: bit 0/1 =
-// "in near list 0/1" (the two near lists alternate between rounds), bit 2 =
-// "in far list". A vertex improved during a round is pushed to the next near
-// list unless its bit for that list is set, so every improvement made during
-// a round is relaxed in the next round, with no ordering needed between the
-// key update and the flag update. Lists therefore never hold a vertex twice
-// and fit in n entries.
+// Dedup of the near lists uses 4 bits per vertex in a flag word array: bit 0/1
+// = "in near list 0/1" (the two near lists alternate between rounds). A vertex
+// improved during a round is pushed to the next near list unless its bit for
+// that list is set, so every improvement made during a round is relaxed in the
+// next round, with no ordering needed between the key update and the flag
+// update. The far list needs no bit: between bucket ends it holds exactly the
+// vertices whose key is at or beyond T, plus some that have dropped below
+// since, so a vertex enters it when it is first reached there. Lists
+// therefore never hold a vertex twice and fit in n entries.
 //
 // Batched form: a persistent kernel, one workgroup per tree; each workgroup
 // owns a slot of per-tree state and pops roots from a rank-ordered work queue
@@ -143,18 +145,26 @@ template <typename K, int WG>
 struct Expand {
     int64_t beg[WG];
     K key[WG];
-    uint32_t off[WG];
-    uint32_t wsum[WG / 64];
+    uint32_t off[WG];         // exclusive scan of the degrees within each wave's vertices
+    uint32_t wtot[WG / 64];   // arcs of each wave's vertices
 };
 
-// Relax every arc of the vertices cur[base .. base+nv) (nv <= WG), balanced
+// Relaxation of the arcs of a chunk of at most WG near vertices, balanced
 // over the block by arc index: thread t handles arcs t, t+WG, ... of the
-// chunk, RELAX_ILP of them at a time so that their loads are in flight
-// together. Improved vertices go to the touched list (the first time they
-// are reached), to the next near list (new distance below T) or to the far
-// list, through wave-aggregated appends on the counters. Every clean key
-// set here raises *umax (largest clean distance so far); clean far pushes
-// are counted in *cnt_far_clean.
+// chunk, RELAX_ILP of them at a time. A tree's rounds are a chain of
+// dependent accesses (list -> key and row -> arc -> target key -> atomic
+// minimum -> list), most of them to lines that no cache holds, so the chain
+// is what bounds them: a step is done for a thread's RELAX_ILP arcs together
+// before the next one begins (owner search, arcs, keys), the candidates
+// among them go through the wave's queue, and the appends to all lists take
+// one atomic instruction per wave. Improved vertices go to the touched list
+// (the first time they are reached), to the next near list (new distance
+// below T) or to the far list. Every clean key set here raises *umax (largest
+// clean distance so far). Measured against one arc after the other with an
+// atomic per list and arc, every step waiting for the one before: unpruned
+// trees of a 512x512 grid 577 -> 455 ms, of R-MAT 15 under a random ranking
+// 185 -> 105 ms, R-MAT 20's unpruned level 17.7 -> 12.3 ms, its pruned team
+// level 10.8 -> 9.2 ms.
 constexpr int RELAX_ILP = 4;
 
 // The root's distances to its prefix hubs as an open-addressing LDS hash
@@ -183,168 +193,383 @@ struct HashLds {
     uint32_t v[C];
 };
 
+// Candidates of a wave: the arcs whose new distance is below the key seen at
+// their target. They are a minority of the arcs, and the pruning test's
+// length differs from one to the next, so they are gathered here and tested
+// and applied 64 at a time, one per lane, instead of each thread taking its
+// own few one after the other with most lanes idle.
+template <typename K>
+struct WaveQueue {
+    K nk[64 * (RELAX_ILP + 1)];
+    int32_t u[64 * (RELAX_ILP + 1)];
+};
+
+// LDS written by some lanes of a wave and read by others: order the wave's
+// accesses (a wave executes in lockstep; this keeps the compiler from moving
+// LDS accesses across the point)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// What a relaxation needs besides the graph and the chunk. A vertex list is
+// a global array; the first lds entries of the next near list may live in
+// LDS instead.
+struct RelaxCtx {
+    int32_t h;                // root
+    int64_t T;                // bucket bound
+    uint32_t nextbit;         // flag of the next near list
+    int32_t* touched;
+    int32_t* next;
+    int32_t* far;
+    int32_t* next_lds;        // entries [0, lds) of the next near list
+    int32_t lds;
+    // rank-prefix pruning
+    bool prune;
+    const int64_t* poff;
+    const uint64_t* plab;
+    const uint32_t* pmin;
+    const uint32_t* dh;
+    const int32_t* hk;        // hashed root distances (keys), or NULL
+    uint32_t pbound;
+    uint32_t dhmin;
+    bool dmaj;
+    bool rank_query;
+};
+
+// The part of a chunk's expansion before its first barrier: the degree scan
+// within the wave. deg = 0 beyond the chunk.
+template <typename K, int WG>
+__device__ __forceinline__ void expand_scan(Expand<K, WG>& X, uint32_t deg) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    uint32_t inc = deg;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d);
+        if (lane >= d) inc += y;
+    }
+    X.off[tid] = inc - deg;
+    if (lane == 63) X.wtot[tid >> 6] = inc;
+}
+
+// Behind that barrier: arcs before each wave's vertices (lane i of the
+// result: wave i; the total beyond the last wave).
+template <typename K, int WG>
+__device__ __forceinline__ uint32_t expand_waves(const Expand<K, WG>& X, uint32_t& total) {
+    constexpr int NW = WG / 64;
+    const int lane = threadIdx.x & 63;
+    const uint32_t x = lane < NW ? X.wtot[lane] : 0u;
+    uint32_t s = x;
+#pragma unroll
+    for (int d = 1; d < NW; d <<= 1) {
+        const uint32_t y = __shfl_up(s, d);
+        if (lane >= d) s += y;
+    }
+    total = __shfl(s, NW - 1);
+    return lane < NW ? s - x : total;
+}
+
+// Append the marked entries of a wave to three lists at once: lanes 0, 1
+// and 2 add the lists' counts to their counters in one atomic instruction.
+// Every lane of the wave must call it.
+template <int N, typename C>
+struct Append3 {
+    uint64_t m[3][N];
+    C base[3];
+    // marks -> list positions; c: the counters, i0..i2 their indexes
+    __device__ __forceinline__ bool reserve(C* c, int i0, int i1, int i2) {
+        uint32_t cnt[3] = {0, 0, 0};
+#pragma unroll
+        for (int l = 0; l < 3; l++)
+#pragma unroll
+            for (int j = 0; j < N; j++) cnt[l] += (uint32_t)__popcll(m[l][j]);
+        if ((cnt[0] | cnt[1] | cnt[2]) == 0) return false;
+        const int lane = threadIdx.x & 63;
+        const uint32_t mine = lane == 0 ? cnt[0] : lane == 1 ? cnt[1] : cnt[2];
+        C r = 0;
+        if (lane < 3 && mine) r = atomicAdd(&c[lane == 0 ? i0 : lane == 1 ? i1 : i2], (C)mine);
+#pragma unroll
+        for (int l = 0; l < 3; l++) base[l] = __shfl(r, l);
+        return true;
+    }
+    __device__ __forceinline__ int64_t at(int l, int j) const {
+        int64_t q = (int64_t)base[l] + lanes_below(m[l][j]);
+#pragma unroll
+        for (int i = 0; i < j; i++) q += __popcll(m[l][i]);
+        return q;
+    }
+};
+
+// Test and apply nc candidates of a wave's queue, one per lane. ctr[it_, in_,
+// if_]: the counters of the touched, next near and far lists.
+template <typename K, int SCOPE, typename C>
+__device__ __forceinline__ void settle(const RGraph& g, K* key, uint32_t* flags, const WaveQueue<K>* Q, int first,
+                                       int nc, const RelaxCtx& cx, C* ctr, int it_, int in_, int if_,
+                                       unsigned long long& my_umax, unsigned long long& my_fmin) {
+    typedef unsigned long long ull;
+    const int lane = threadIdx.x & 63;
+    bool cand = lane < nc;
+    int32_t u = 0;
+    K nk = 0;
+    if (cand) { u = Q->u[first + lane]; nk = Q->nk[first + lane]; }
+    const uint64_t nd = (uint64_t)(nk >> 1);
+    if (cx.prune) {
+        // Rank-prefix pruning (Section 4.3): the labels of the hubs
+        // [0, pbound), complete because their trees are done, give the
+        // length of the shortest root-u walk through each of them (dh holds
+        // the root's side). If one is no longer than the candidate, the
+        // candidate is either not a shortest path or a shortest path through
+        // a hub that outranks the root; either way it cannot lead to a label,
+        // and a vertex whose true key is clean never has such a hub on its
+        // shortest paths, so dropping the candidate changes no label. No walk
+        // through a prefix hub is shorter than the root's nearest prefix hub
+        // plus u's: below that bound u's group is not read.
+        int64_t i = 0, le = 0;
+        if (cand && (uint64_t)cx.dhmin + (cx.pmin ? cx.pmin[u] : 0u) <= nd) {
+            i = cx.poff[u];
+            le = cx.poff[u + 1];
+        }
+        // u's entries are read 8 at a time until one prunes
+#pragma unroll 1
+        for (; i < le && cand; i += 8) {
+            uint64_t lx[8];
+#pragma unroll
+            for (int z = 0; z < 8; z++) lx[z] = i + z < le ? cx.plab[i + z] : ~0ull;
+#pragma unroll
+            for (int z = 0; z < 8; z++) {
+                const uint32_t x = cx.dmaj ? (uint32_t)lx[z] : (uint32_t)(lx[z] >> 32);
+                const uint32_t dd = cx.dmaj ? (uint32_t)(lx[z] >> 32) : (uint32_t)lx[z];
+                if (x >= cx.pbound) continue;
+                const uint32_t da = cx.hk ? hash_lookup(cx.hk, cx.dh, x) : cx.dh[x];
+                if (da != 0xFFFFFFFFu && (uint64_t)da + dd <= nd) cand = false;
+            }
+            // groups ordered by distance: no later entry is closer
+            if (cx.dmaj && (uint64_t)(uint32_t)(lx[7] >> 32) + cx.dhmin > nd) break;
+        }
+    }
+    K old = 0;
+    if (cand) old = amin<SCOPE>(&key[u], nk);
+    const bool imp = cand && nk < old, near = imp && (int64_t)nd < cx.T;
+    const bool first_visit = imp && old == KeyTraits<K>::INF;
+    uint32_t o = 0;
+    if (near) o = aor<SCOPE>(&flags[u >> 3], cx.nextbit << fshift(u));
+    if (imp && (nk & 1)) my_umax = my_umax > nd ? my_umax : (ull)nd;
+    if (imp && !near) my_fmin = my_fmin < nd ? my_fmin : (ull)nd;
+    Append3<1, C> ap;
+    ap.m[0][0] = __ballot(first_visit);
+    ap.m[1][0] = __ballot(near && (o >> fshift(u) & cx.nextbit) == 0);
+    // a reached vertex whose key is at or beyond T is in the far list
+    // already, so only a first visit lists it there
+    ap.m[2][0] = __ballot(first_visit && !near);
+    if (!ap.reserve(ctr, it_, in_, if_)) return;
+    if (ap.m[0][0] >> lane & 1) {
+        const int64_t q = ap.at(0, 0);
+        if (q < g.n) lput<SCOPE>(&cx.touched[q], u);
+    }
+    if (ap.m[1][0] >> lane & 1) {
+        const int64_t q = ap.at(1, 0);
+        if (q < cx.lds) cx.next_lds[q] = u;
+        else if (q < g.n) lput<SCOPE>(&cx.next[q], u);
+    }
+    if (ap.m[2][0] >> lane & 1) {
+        const int64_t q = ap.at(2, 0);
+        if (q < g.n) lput<SCOPE>(&cx.far[q], u);
+    }
+}
+
+// ctr[it_, in_, if_]: the counters of the touched, next near and far lists.
+// fmin (may be NULL): lower bound of the distances in the far list. Q: the
+// wave's queue.
 template <typename K, int WG, int SCOPE, typename C>
-__device__ __forceinline__ void relax_block(const RGraph& g, K* key, uint32_t* flags,
-                                            const int32_t* cur, int32_t base, int32_t nv,
-                                            uint32_t curbit, uint32_t nextbit, int32_t h,
-                                            int64_t T, int32_t* touched, int32_t* next,
-                                            int32_t* far, C* cnt_touched, C* cnt_next,
-                                            C* cnt_far, C* cnt_far_clean, unsigned long long* umax,
-                                            const int64_t* poff, const uint64_t* plab, uint32_t pbound,
-                                            const uint32_t* dh, Expand<K, WG>& X, uint64_t& arcs,
-                                            bool rank_query = false, const uint32_t* pmin = nullptr,
-                                            uint32_t dhmin = 0, bool dmaj = false,
-                                            const int32_t* hk = nullptr) {
+__device__ __forceinline__ void relax_arcs(const RGraph& g, K* key, uint32_t* flags, const Expand<K, WG>& X,
+                                           int32_t nv, uint32_t wpre, uint32_t total, const RelaxCtx& cx,
+                                           C* ctr, int it_, int in_, int if_, unsigned long long* umax,
+                                           unsigned long long* fmin, WaveQueue<K>* Q) {
+    typedef unsigned long long ull;
+    const int tid = threadIdx.x, lane = tid & 63;
+    ull my_umax = 0, my_fmin = ~0ull;
+    int nq = 0;
+    // first steps of the owner search: over the waves, then within one
+    const int nw = (nv + 63) >> 6;
+    const int wtop = nw > 1 ? 1 << (31 - __clz(nw - 1)) : 0;
+    const int n1 = min(nv, 64);
+    const int ltop = n1 > 1 ? 1 << (31 - __clz(n1 - 1)) : 0;
+#pragma unroll 1
+    for (uint32_t eb = (uint32_t)(tid & ~63); eb < total; eb += WG * RELAX_ILP) {
+        int32_t u[RELAX_ILP];
+        K nk[RELAX_ILP], old[RELAX_ILP];
+        bool cand[RELAX_ILP];
+        {
+            int own[RELAX_ILP];
+            uint32_t rel[RELAX_ILP];
+            uint64_t a[RELAX_ILP];
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) own[j] = 0;
+#pragma unroll 1
+            for (int s = wtop; s > 0; s >>= 1)
+#pragma unroll
+                for (int j = 0; j < RELAX_ILP; j++) {
+                    const int t = own[j] + s;
+                    if (__shfl(wpre, t) <= eb + j * WG + lane) own[j] = t;
+                }
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) {
+                rel[j] = eb + j * WG + lane - __shfl(wpre, own[j]);
+                own[j] = (own[j] * 64) & (WG - 1);    // (beyond the last arc: any vertex)
+            }
+#pragma unroll 1
+            for (int s = ltop; s > 0; s >>= 1)
+#pragma unroll
+                for (int j = 0; j < RELAX_ILP; j++)
+                    if (X.off[own[j] + s] <= rel[j]) own[j] += s;
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) {
+                const uint32_t e = eb + j * WG + lane;
+                a[j] = e < total ? g.arc[X.beg[own[j]] + (rel[j] - X.off[own[j]])] : 0;
+                nk[j] = X.key[own[j]];
+            }
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) {
+                u[j] = (int32_t)(a[j] >> 32);
+                nk[j] = pack<K>((uint64_t)(nk[j] >> 1) + (uint32_t)a[j],
+                                (uint32_t)(nk[j] & 1) & (uint32_t)(u[j] > cx.h));
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < RELAX_ILP; j++) {
+            const uint32_t e = eb + j * WG + lane;
+            old[j] = e < total ? ld<SCOPE>(&key[u[j]]) : (K)0;
+        }
+#pragma unroll
+        for (int j = 0; j < RELAX_ILP; j++) {
+            // Keys only decrease, so a value read earlier is never below the
+            // current one: when the candidate is not below it, the atomic
+            // would fail and is skipped. (Beyond the last arc the key read is 0.)
+            cand[j] = nk[j] < old[j];
+            // rank query of the pruned construction (Algorithm 1): a vertex
+            // that outranks the root is neither labelled nor expanded
+            if (cx.rank_query && u[j] < cx.h) cand[j] = false;
+        }
+#pragma unroll
+        for (int j = 0; j < RELAX_ILP; j++) {
+            const uint64_t m = __ballot(cand[j]);
+            const int q = nq + (int)lanes_below(m);
+            if (cand[j]) { Q->nk[q] = nk[j]; Q->u[q] = u[j]; }
+            nq += (int)__popcll(m);
+        }
+        wave_sync();
+#pragma unroll 1
+        for (; nq >= 64; nq -= 64)
+            settle<K, SCOPE, C>(g, key, flags, Q, nq - 64, 64, cx, ctr, it_, in_, if_, my_umax, my_fmin);
+        wave_sync();
+    }
+    if (nq > 0) settle<K, SCOPE, C>(g, key, flags, Q, 0, nq, cx, ctr, it_, in_, if_, my_umax, my_fmin);
+    // one maximum per wave; the bounds only move one way, so a value read
+    // earlier filters correctly
+    if (SCOPE == __HIP_MEMORY_SCOPE_WORKGROUP) {
+        if (my_umax > *umax) atomicMax(umax, my_umax);
+        if (fmin && my_fmin < *fmin) atomicMin(fmin, my_fmin);
+    } else {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            const ull y = __shfl_xor(my_umax, d);
+            my_umax = y > my_umax ? y : my_umax;
+        }
+        if (lane == 0 && my_umax) atomicMax(umax, my_umax);
+    }
+}
+
+// Expand the vertices cur[base .. base+nv) (nv <= WG) of a near list that
+// several workgroups share (team and plain forms).
+template <typename K, int WG, int SCOPE, typename C>
+__device__ __forceinline__ void relax_block(const RGraph& g, K* key, uint32_t* flags, const int32_t* cur,
+                                            int32_t base, int32_t nv, uint32_t curbit, const RelaxCtx& cx, C* ctr,
+                                            int it_, int in_, int if_, unsigned long long* umax, Expand<K, WG>& X,
+                                            WaveQueue<K>* Q, uint64_t& arcs) {
     const int tid = threadIdx.x;
     uint32_t deg = 0;
     if (tid < nv) {
-        int32_t v = lget<SCOPE>(&cur[base + tid], g.n);
+        const int32_t v = lget<SCOPE>(&cur[base + tid], g.n);
         aand<SCOPE>(&flags[v >> 3], ~(curbit << fshift(v)));
-        K kv = ld<SCOPE>(&key[v]);
-        int64_t b = g.row[v];
+        const int64_t b = g.row[v];
         deg = (uint32_t)(g.row[v + 1] - b);
         X.beg[tid] = b;
-        X.key[tid] = kv;
+        X.key[tid] = ld<SCOPE>(&key[v]);
     }
-    uint32_t total;
-    uint32_t ex = block_scan<WG>(deg, X.wsum, total);
-    X.off[tid] = ex;
+    expand_scan<K, WG>(X, deg);
     __syncthreads();
+    uint32_t total;
+    const uint32_t wpre = expand_waves<K, WG>(X, total);
     arcs += total;
-    unsigned long long my_umax = 0;
-    bool my_umax_set = false;
-    for (uint32_t e0 = tid; e0 < total; e0 += WG * RELAX_ILP) {
-        int own[RELAX_ILP];
-        uint64_t a[RELAX_ILP];
-        K seen[RELAX_ILP];
-#pragma unroll
-        for (int j = 0; j < RELAX_ILP; j++) {
-            const uint32_t e = e0 + j * WG;
-            int lo = 0, hi = nv - 1;
-            while (lo < hi) {
-                int mid = (lo + hi + 1) >> 1;
-                if (X.off[mid] <= e) lo = mid; else hi = mid - 1;
-            }
-            own[j] = lo;
-        }
-#pragma unroll
-        for (int j = 0; j < RELAX_ILP; j++) {
-            const uint32_t e = e0 + j * WG;
-            a[j] = e < total ? g.arc[X.beg[own[j]] + (e - X.off[own[j]])] : 0;
-        }
-#pragma unroll
-        for (int j = 0; j < RELAX_ILP; j++) {
-            const uint32_t e = e0 + j * WG;
-            seen[j] = e < total ? ld<SCOPE>(&key[(int32_t)(a[j] >> 32)]) : (K)0;
-        }
-#pragma unroll
-        for (int j = 0; j < RELAX_ILP; j++) {
-            const uint32_t e = e0 + j * WG;
-            const bool valid = e < total;
-            const int32_t u = (int32_t)(a[j] >> 32);
-            const K kv = X.key[own[j]];
-            const uint64_t nd = (uint64_t)(kv >> 1) + (uint32_t)a[j];
-            const K nk = pack<K>(nd, (uint32_t)(kv & 1) & (uint32_t)(u > h));
-            // Keys only decrease, so a value read earlier is never below the
-            // current one: when the candidate is not below it, the atomic
-            // would fail and is skipped.
-            bool cand = valid && nk < seen[j];
-            // rank query of the pruned construction (Algorithm 1): a vertex
-            // that outranks the root is neither labelled nor expanded
-            if (rank_query && u < h) cand = false;
-            // no walk through a prefix hub is shorter than the root's nearest
-            // prefix hub plus u's: below that bound u's group is not read
-            if (cand && dh && (!pmin || (uint64_t)dhmin + pmin[u] <= nd)) {
-                // Rank-prefix pruning (Section 4.3): the labels of the hubs
-                // [0, pbound), complete because their trees are done, give the
-                // length of the shortest root-u walk through each of them
-                // (dh holds the root's side). If one is no longer than the
-                // candidate, the candidate is either not a shortest path or a
-                // shortest path through a hub that outranks the root; either
-                // way it cannot lead to a label, and a vertex whose true key
-                // is clean never has such a hub on its shortest paths, so
-                // dropping the candidate changes no label. u's entries are read
-                // 8 at a time until one prunes.
-                const int64_t lb = poff[u], le = poff[u + 1];
-                for (int64_t i = lb; i < le && cand; i += 8) {
-                    uint64_t lx[8];
-#pragma unroll
-                    for (int z = 0; z < 8; z++) lx[z] = i + z < le ? plab[i + z] : ~0ull;
-#pragma unroll
-                    for (int z = 0; z < 8; z++) {
-                        const uint32_t x = dmaj ? (uint32_t)lx[z] : (uint32_t)(lx[z] >> 32);
-                        const uint32_t dd = dmaj ? (uint32_t)(lx[z] >> 32) : (uint32_t)lx[z];
-                        if (x >= pbound) continue;
-                        const uint32_t a = hk ? hash_lookup(hk, dh, x) : dh[x];
-                        if (a != 0xFFFFFFFFu && (uint64_t)a + dd <= nd) cand = false;
-                    }
-                    // groups ordered by distance: no later entry is closer
-                    if (dmaj && (uint64_t)(uint32_t)(lx[7] >> 32) + dhmin > nd) break;
-                }
-            }
-            K old = seen[j];
-            if (cand) old = amin<SCOPE>(&key[u], nk);
-            const bool imp = cand && nk < old;
-            const bool first = imp && old == KeyTraits<K>::INF;
-            const bool tonear = imp && (int64_t)nd < T;
-            bool pnear = false, pfar = false;
-            if (imp) {
-                if (nk & 1) { my_umax = my_umax > nd ? my_umax : nd; my_umax_set = true; }
-                uint32_t bit = (tonear ? nextbit : FAR_BIT) << fshift(u);
-                uint32_t o = aor<SCOPE>(&flags[u >> 3], bit);
-                bool fresh = (o & bit) == 0;
-                pnear = fresh && tonear;
-                pfar = fresh && !tonear;
-            }
-            int64_t q = wave_append(first, cnt_touched);
-            if (first && q < g.n) lput<SCOPE>(&touched[q], u);
-            q = wave_append(pnear, cnt_next);
-            if (pnear && q < g.n) lput<SCOPE>(&next[q], u);
-            q = wave_append(pfar, cnt_far);
-            if (pfar && q < g.n) lput<SCOPE>(&far[q], u);
-            const bool pfc = pfar && (nk & 1);
-            (void)wave_append(pfc, cnt_far_clean);
-        }
-    }
-    if (my_umax_set) atomicMax(umax, my_umax);
+    relax_arcs<K, WG, SCOPE, C>(g, key, flags, X, nv, wpre, total, cx, ctr, it_, in_, if_, umax, nullptr, Q);
     __syncthreads();
 }
 
 // ---------------------------------------------------------------- batched
+// What a bucket's end finds out about the far list.
+struct BucketEnd {
+    int32_t moved, kept;          // entries for the next bucket, entries that stay
+    int32_t clean;                // some live entry is clean
+    unsigned long long kmin;      // lower bound of the distances that stay
+};
+
+// counters of the lists, S.ctr
+enum { B_NEXT = 0, B_FAR = 3, B_TOUCHED = 4, B_CTRS = 5 };   // near counts rotate by round % 3
+
+// Entries of a near list held in LDS; the rest of a longer list is in global
+// memory. Most rounds of a tree expand fewer vertices than that, and then
+// the list costs neither a store to wait for nor a load.
+template <int WG>
+constexpr int near_lds() { return WG; }
+
 template <typename K, int WG>
 struct BatchedLds {
     Expand<K, WG> X;
+    int32_t nl[2][near_lds<WG>()];
     unsigned long long red64[WG / 64];
     int32_t red32[WG / 64];
-    int32_t ncur, cnt_next, cnt_far, cnt_touched, nkeep, far_clean;
+    unsigned long long wmin[WG / 64];
+    uint32_t wcl[WG / 64];
+    int32_t ctr[B_CTRS];
+    int32_t nkeep;
+    BucketEnd be[2];
     int32_t root;
     int32_t bnext, bend;      // root queue positions taken by this workgroup, not yet grown
     uint32_t dhmin;           // smallest distance of the root to a prefix hub
-    unsigned long long umax;
+    unsigned long long umax;  // largest clean distance set so far
+    unsigned long long fmin;  // lower bound of the distances in the far list
     long long pool_base;
 };
 
+template <typename K, int WG>
+__device__ __forceinline__ int32_t near_get(const BatchedLds<K, WG>& S, int par, const int32_t* glob, int32_t i) {
+    int32_t v = S.nl[par][min(i, near_lds<WG>() - 1)];
+    if (i >= near_lds<WG>()) v = glob[i];
+    return v;
+}
+
 // Early termination between rounds. Pending vertices are the current near
-// list and the far list. If none of them is clean, and no pending distance
+// list and the far list. If no near vertex is clean, and no pending distance
 // can be at or below the largest clean distance ever set (umax), no later
 // relaxation can create or change a clean key: every vertex whose true key
 // is clean already has it (the first unfinished vertex on a shortest path to
 // it would be pending and clean), and every clean key is final. The pending
 // distances are bounded below by the smallest near key and by T (far
 // entries hold distances >= T; a far vertex whose key dropped below T has
-// been pushed to the near list as well). far_clean counts clean pushes to
-// the far list since the last filter, an upper bound of its clean entries.
+// been pushed to the near list as well), so the test can only hold while
+// umax < T, and then no far entry is clean either. A near list of at most WG
+// vertices is tested while it is expanded (its keys are in registers then);
+// a longer one by may_stop beforehand.
 template <typename K, int WG, int SC>
-__device__ __forceinline__ bool may_stop(BatchedLds<K, WG>& S, const K* key, const int32_t* cur,
+__device__ __forceinline__ bool may_stop(BatchedLds<K, WG>& S, const K* key, int par, const int32_t* cur,
                                          int32_t ncur, int64_t T) {
     constexpr int NW = WG / 64;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    // one reduction of (smallest pending distance, any pending vertex clean):
-    // the distance in the high bits, the clean flag in bit 0 of the OR half
     unsigned long long mn = ~0ull;
     int32_t cl = 0;
     for (int32_t i = tid; i < ncur; i += WG) {
-        K kv = ld<SC>(const_cast<K*>(&key[cur[i]]));
+        K kv = ld<SC>(const_cast<K*>(&key[near_get<K, WG>(S, par, cur, i)]));
         unsigned long long d = (unsigned long long)(kv >> 1);
         mn = d < mn ? d : mn;
         cl |= (int32_t)(kv & 1);
@@ -376,21 +601,31 @@ __device__ __forceinline__ bool may_stop(BatchedLds<K, WG>& S, const K* key, con
 // tree's pool range recorded in p.rlab for the cleaning that follows.
 // PRUNE: rank-prefix pruning with p.poff / p.plab; the root's distances to
 // the prefix hubs live in dynamic LDS (p.pbound words) below phase 3.
+//
+// A round takes two barriers besides the one that ends it only when its list
+// is longer than the workgroup; a bucket's end takes one pass over the far
+// list and one barrier. The three global lists change roles: a bucket's end
+// writes what stays in the far list to the free near buffer.
 template <typename K, int WG, int PHASE, bool PRUNE, bool HS>
-__global__ __launch_bounds__(WG) void k_tree_batched(TreeParams p) {
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_tree_batched(TreeParams p) {
     constexpr int SC = __HIP_MEMORY_SCOPE_WORKGROUP;
     constexpr bool HYB = PHASE == 3;
+    constexpr int NW = WG / 64;
+    typedef unsigned long long ull;
     __shared__ BatchedLds<K, WG> S;
+    __shared__ WaveQueue<K> Q[NW];
     __shared__ HashLds<HS ? HCAP : 1> H;
     extern __shared__ uint32_t dh_lds[];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t slot = blockIdx.x;
     uint32_t* dh = HYB ? p.dhg + slot * p.s.stride : HS ? H.v : dh_lds;
     K* key = (K*)p.s.key + slot * p.s.stride;
     uint32_t* flags = p.s.flags + slot * p.s.fstride;
     int32_t* touched = p.s.touched + slot * p.s.stride;
-    int32_t* lists = p.s.lists + slot * 3 * p.s.stride;
-    int32_t* far = lists + 2 * p.s.stride;
+    // near list of this round, of the next one, far list
+    int32_t* cur = p.s.lists + slot * 3 * p.s.stride;
+    int32_t* next = cur + p.s.stride;
+    int32_t* far = next + p.s.stride;
     const int64_t delta = p.delta;
     // dh is all ones between trees: a tree sets its root's entries and
     // clears them when it is done (the global array of phase 3 is set to
@@ -423,6 +658,16 @@ __global__ __launch_bounds__(WG) void k_tree_batched(TreeParams p) {
             }
             S.root = r;
             S.dhmin = 0xFFFFFFFFu;
+            if (r >= 0) {
+                // the root, with key (0, clean), is the near list of round 0
+                S.nl[0][0] = r;
+                touched[0] = r;
+                for (int i = 0; i < B_CTRS; i++) S.ctr[i] = 0;
+                S.ctr[B_TOUCHED] = 1;
+                S.be[0] = S.be[1] = BucketEnd{0, 0, 0, ~0ull};
+                S.umax = 0;
+                S.fmin = ~0ull;
+            }
         }
         __syncthreads();
         const int32_t h = S.root;
@@ -437,7 +682,8 @@ __global__ __launch_bounds__(WG) void k_tree_batched(TreeParams p) {
             __syncthreads();
             continue;
         }
-        if (prune)
+        if (tid == 0) st<SC>(&key[h], pack<K>(0, 1));
+        if (prune) {
             for (int64_t i = p.poff[hg] + tid; i < p.poff[hg + 1]; i += WG) {
                 const uint64_t lx = p.plab[i];
                 const uint32_t x = p.dmaj ? (uint32_t)lx : (uint32_t)(lx >> 32), y = x ^ px;
@@ -453,121 +699,201 @@ __global__ __launch_bounds__(WG) void k_tree_batched(TreeParams p) {
                     atomicMin(&S.dhmin, dd);
                 }
             }
-
-        // ---- init: root key (0, clean) in near list 0
-        if (tid == 0) {
-            st<SC>(&key[h], pack<K>(0, 1));
-            touched[0] = h;
-            lists[0] = h;
-            aor<SC>(&flags[h >> 3], 1u << fshift(h));
-            S.ncur = 1; S.cnt_next = 0; S.cnt_far = 0; S.cnt_touched = 1;
-            S.far_clean = 0; S.umax = 0;
+            __syncthreads();
         }
-        __syncthreads();
+
         int64_t T = delta;
-        int it = 0;
+        int it = 0, nbucket = 0;
+        int32_t ncur = 1;
         uint64_t arcs = 0, settled = 0;
         const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
         bool early = false;
+        RelaxCtx cx;
+        cx.h = h;
+        cx.touched = touched;
+        cx.lds = near_lds<WG>();
+        cx.poff = p.poff;
+        cx.plab = p.plab;
+        cx.pmin = p.pmin;
+        cx.prune = prune;
+        cx.dh = dh;
+        cx.hk = HS ? H.k : nullptr;
+        cx.pbound = (uint32_t)p.pbound;
+        cx.dhmin = S.dhmin;
+        cx.dmaj = p.dmaj != 0;
+        cx.rank_query = HYB;
         for (;;) {
             // ---- rounds inside the bucket until no near vertex is left
             bool stopped = false;
-            for (;;) {
-                const int32_t ncur = S.ncur;
-                const uint32_t curbit = 1u << (it & 1), nextbit = 1u << ((it + 1) & 1);
-                int32_t* cur = lists + (int64_t)(it & 1) * p.s.stride;
-                int32_t* next = lists + (int64_t)((it + 1) & 1) * p.s.stride;
+            while (ncur > 0) {
+                const int par = it & 1;
+                const uint32_t curbit = 1u << par, nextbit = 2u >> par;
+                cx.T = T;
+                cx.nextbit = nextbit;
+                cx.next = next;
+                cx.far = far;
+                cx.next_lds = S.nl[par ^ 1];
+                // the counter that round it + 1 appends to (read last when
+                // round it - 1 began)
+                if (tid == 0) S.ctr[B_NEXT + (it + 2) % 3] = 0;
                 // (the first round holds only the root, which is clean)
-                if (p.early_term && it > 0 && S.far_clean == 0 && may_stop<K, WG, SC>(S, key, cur, ncur, T)) {
+                const ull um = S.umax;
+                const bool test = p.early_term && it > 0 && um < (ull)T;
+                if (test && ncur > WG && may_stop<K, WG, SC>(S, key, par, cur, ncur, T)) {
                     // drop the pending entries: clear their list bits
-                    for (int32_t i = tid; i < ncur; i += WG) aand<SC>(&flags[cur[i] >> 3], ~(curbit << fshift(cur[i])));
-                    for (int32_t i = tid; i < S.cnt_far; i += WG) aand<SC>(&flags[far[i] >> 3], ~(FAR_BIT << fshift(far[i])));
-                    early = ncur > 0 || S.cnt_far > 0;
+                    for (int32_t i = tid; i < ncur; i += WG) {
+                        const int32_t v = near_get<K, WG>(S, par, cur, i);
+                        aand<SC>(&flags[v >> 3], ~(curbit << fshift(v)));
+                    }
                     stopped = true;
-                    __syncthreads();
                     break;
                 }
                 settled += ncur;
-                for (int32_t base = 0; base < ncur; base += WG)
-                    relax_block<K, WG, SC>(p.g, key, flags, cur, base, min(WG, ncur - base), curbit,
-                                           nextbit, h, T, touched, next, far, &S.cnt_touched,
-                                           &S.cnt_next, &S.cnt_far, &S.far_clean, &S.umax, p.poff,
-                                           p.plab, (uint32_t)p.pbound, prune ? dh : nullptr, S.X, arcs, HYB,
-                                           p.pmin, S.dhmin, p.dmaj != 0, HS ? H.k : nullptr);
+#pragma unroll 1
+                for (int32_t base = 0; base < ncur; base += WG) {
+                    const int32_t nv = min(WG, ncur - base);
+                    uint32_t deg = 0;
+                    ull mn = ~0ull;
+                    uint32_t cl = 0;
+                    if (tid < nv) {
+                        const int32_t v = near_get<K, WG>(S, par, cur, base + tid);
+                        K kv = pack<K>(0, 1);
+                        if (it > 0) {
+                            aand<SC>(&flags[v >> 3], ~(curbit << fshift(v)));
+                            kv = ld<SC>(&key[v]);
+                        }
+                        const int64_t b = p.g.row[v];
+                        deg = (uint32_t)(p.g.row[v + 1] - b);
+                        S.X.beg[tid] = b;
+                        S.X.key[tid] = kv;
+                        mn = (ull)(kv >> 1);
+                        cl = (uint32_t)(kv & 1);
+                    }
+                    expand_scan<K, WG>(S.X, deg);
+                    if (test && ncur <= WG) {
+                        const bool anycl = __ballot(cl != 0) != 0;
+#pragma unroll
+                        for (int d = 32; d >= 1; d >>= 1) {
+                            const ull y = __shfl_xor(mn, d);
+                            mn = y < mn ? y : mn;
+                        }
+                        if (lane == 0) { S.wmin[w] = mn; S.wcl[w] = anycl; }
+                    }
+                    __syncthreads();
+                    uint32_t total;
+                    const uint32_t wpre = expand_waves<K, WG>(S.X, total);
+                    if (test && ncur <= WG) {
+                        mn = (ull)T;
+                        cl = 0;
+#pragma unroll
+                        for (int i = 0; i < NW; i++) {
+                            mn = S.wmin[i] < mn ? S.wmin[i] : mn;
+                            cl |= S.wcl[i];
+                        }
+                        // (the vertices' list bits are cleared already)
+                        if (cl == 0 && mn > um) { stopped = true; break; }
+                    }
+                    arcs += total;
+                    relax_arcs<K, WG, SC, int32_t>(p.g, key, flags, S.X, nv, wpre, total, cx, S.ctr,
+                                                          B_TOUCHED, B_NEXT + (it + 1) % 3, B_FAR, &S.umax,
+                                                          &S.fmin, &Q[w]);
+                    if (base + WG < ncur) __syncthreads();      // X is used again
+                }
+                if (stopped) { settled -= ncur; break; }
                 __syncthreads();
                 it++;
-                if (tid == 0) { S.ncur = S.cnt_next; S.cnt_next = 0; }
-                __syncthreads();
-                if (S.ncur == 0) break;
+                ncur = S.ctr[B_NEXT + it % 3];
+                int32_t* t = cur; cur = next; next = t;
             }
-            if (stopped) break;
-            // ---- bucket done: drop settled far entries, find the smallest
-            //      pending distance and whether any pending vertex is clean
-            int32_t nfar = S.cnt_far;
-            // nothing pending at all (most trees of the main phase end so):
-            // the tree is complete without the filter's reductions
+            if (stopped) { early = true; break; }
+            // ---- bucket done: one pass over the far list drops the settled
+            //      entries, moves those of the next bucket to the near list
+            //      and keeps the rest. The next bucket is the one of fmin, a
+            //      lower bound of the pending distances (an entry that set it
+            //      may have moved nearer: then the bucket is empty and the
+            //      pass, which computes the bound anew, runs again).
+            const int32_t nfar = S.ctr[B_FAR];
+            // nothing pending at all (most trees of the main phase end so)
             if (nfar == 0) break;
-            if (tid == 0) { S.nkeep = 0; }
-            __syncthreads();
-            unsigned long long mymin = ~0ull;
-            int32_t myclean = 0;
+            const int64_t Tn = (int64_t)(S.fmin / (ull)delta + 1) * delta;
+            BucketEnd& be = S.be[nbucket & 1];
+            const int par = it & 1;
+            const uint32_t curbit = 1u << par;
+            ull kmin = ~0ull;
+            bool clean = false;
+#pragma unroll 1
             for (int32_t base = 0; base < nfar; base += WG) {
                 const int32_t i = base + tid;
-                bool keep = false;
+                bool tonear = false, keep = false;
                 int32_t v = 0;
-                K kv = 0;
                 if (i < nfar) {
                     v = far[i];
-                    aand<SC>(&flags[v >> 3], ~(FAR_BIT << fshift(v)));
-                    kv = ld<SC>(&key[v]);
-                    keep = (int64_t)(kv >> 1) >= T;
+                    const K kv = ld<SC>(&key[v]);
+                    const int64_t d = (int64_t)(kv >> 1);
+                    tonear = d >= T && d < Tn;
+                    keep = d >= T && d >= Tn;
+                    clean |= (tonear || keep) && (kv & 1);
+                    if (keep) kmin = (ull)d < kmin ? (ull)d : kmin;
                 }
-                __syncthreads();                         // chunk read before compaction writes
-                int64_t q = wave_append(keep, &S.nkeep);
-                if (keep) {
-                    far[q] = v;
-                    mymin = min(mymin, (unsigned long long)(kv >> 1));
-                    myclean += (int32_t)(kv & 1);
+                Append3<1, int32_t> ap;
+                ap.m[0][0] = __ballot(tonear);
+                ap.m[1][0] = __ballot(keep);
+                ap.m[2][0] = 0;
+                if (!ap.reserve(&be.moved, 0, 1, 0)) continue;
+                if (tonear) {
+                    const int32_t q = (int32_t)ap.at(0, 0);
+                    if (q < near_lds<WG>()) S.nl[par][q] = v; else cur[q] = v;
+                    aor<SC>(&flags[v >> 3], curbit << fshift(v));
                 }
-                __syncthreads();
+                if (keep) next[ap.at(1, 0)] = v;
             }
-            unsigned long long mn = block_reduce<WG>(mymin, S.red64, ~0ull,
-                [](unsigned long long a, unsigned long long b) { return a < b ? a : b; });
-            int32_t ncl = block_reduce<WG>(myclean, S.red32, 0, [](int32_t a, int32_t b) { return a + b; });
-            nfar = S.nkeep;
-            if (nfar == 0 || (p.early_term && ncl == 0)) { early = nfar > 0; break; }
-            // ---- next bucket: the one holding the smallest pending distance
-            T = ((int64_t)mn / delta + 1) * delta;
-            int32_t* cur = lists + (int64_t)(it & 1) * p.s.stride;
-            const uint32_t curbit = 1u << (it & 1);
-            if (tid == 0) { S.ncur = 0; S.cnt_far = 0; S.far_clean = 0; }
+            if (__ballot(clean) && lane == 0) be.clean = 1;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) {
+                const ull y = __shfl_xor(kmin, d);
+                kmin = y < kmin ? y : kmin;
+            }
+            if (lane == 0 && kmin != ~0ull) atomicMin(&be.kmin, kmin);
             __syncthreads();
-            for (int32_t base = 0; base < nfar; base += WG) {
-                const int32_t i = base + tid;
-                int32_t v = 0;
-                bool tonear = false, tofar = false, fclean = false;
-                if (i < nfar) {
-                    v = far[i];
-                    K kv = ld<SC>(&key[v]);
-                    tonear = (int64_t)(kv >> 1) < T;
-                    tofar = !tonear;
-                    fclean = tofar && (kv & 1);
-                }
-                __syncthreads();
-                int64_t q = wave_append(tonear, &S.ncur);
-                if (tonear) { cur[q] = v; aor<SC>(&flags[v >> 3], curbit << fshift(v)); }
-                q = wave_append(tofar, &S.cnt_far);
-                if (tofar) { far[q] = v; aor<SC>(&flags[v >> 3], FAR_BIT << fshift(v)); }
-                (void)wave_append(fclean, &S.far_clean);
-                __syncthreads();
+            ncur = be.moved;
+            const int32_t nkept = be.kept;
+            const bool anyclean = be.clean != 0;
+            // (the other record was read behind an earlier barrier)
+            if (tid == 0) {
+                S.ctr[B_FAR] = nkept;
+                S.fmin = be.kmin;
+                S.be[(nbucket + 1) & 1] = BucketEnd{0, 0, 0, ~0ull};
             }
+            if (ncur + nkept == 0) break;
+            if (p.early_term && !anyclean) {
+                early = true;
+                for (int32_t i = tid; i < ncur; i += WG) {
+                    const int32_t v = near_get<K, WG>(S, par, cur, i);
+                    aand<SC>(&flags[v >> 3], ~(curbit << fshift(v)));
+                }
+                break;
+            }
+            T = Tn;
+            nbucket++;
+            int32_t* t = far; far = next; next = t;
+            if (ncur == 0) __syncthreads();
         }
-        // far entries left behind have had their far bit cleared
+        __syncthreads();
 
         // ---- emit labels of clean vertices, reset the slot
-        const int32_t nt = S.cnt_touched;
+        const int32_t nt = S.ctr[B_TOUCHED];
         int32_t mycnt = 0;
-        for (int32_t i = tid; i < nt; i += WG) mycnt += (int32_t)(ld<SC>(&key[touched[i]]) & 1);
+#pragma unroll 1
+        for (int32_t i = tid; i < nt; i += WG * RELAX_ILP) {
+            int32_t v[RELAX_ILP];
+            K kv[RELAX_ILP];
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) v[j] = i + j * WG < nt ? touched[i + j * WG] : -1;
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) kv[j] = v[j] >= 0 ? ld<SC>(&key[v[j]]) : (K)0;
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) mycnt += (int32_t)(kv[j] & 1);
+        }
         const int32_t nl = block_reduce<WG>(mycnt, S.red32, 0, [](int32_t a, int32_t b) { return a + b; });
         if (tid == 0) {
             unsigned long long b = atomicAdd(p.pool.cursor, (unsigned long long)nl);
@@ -585,25 +911,40 @@ __global__ __launch_bounds__(WG) void k_tree_batched(TreeParams p) {
         __syncthreads();
         const long long pb = S.pool_base;
         bool ovf = false;
-        for (int32_t base = 0; base < nt; base += WG) {
-            const int32_t i = base + tid;
-            bool lab = false;
-            int32_t v = 0;
-            uint64_t d = 0;
-            if (i < nt) {
-                v = touched[i];
-                K kv = ld<SC>(&key[v]);
-                lab = (kv & 1) != 0;
-                d = (uint64_t)(kv >> 1);
-                st<SC>(&key[v], KeyTraits<K>::INF);
+#pragma unroll 1
+        for (int32_t base = 0; base < nt; base += WG * RELAX_ILP) {
+            int32_t v[RELAX_ILP];
+            K kv[RELAX_ILP];
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) {
+                const int32_t i = base + j * WG + tid;
+                v[j] = i < nt ? touched[i] : -1;
             }
-            int64_t q = wave_append(lab, &S.nkeep);
-            if (lab && pb >= 0) {
-                ovf |= d > 0x7FFFFFFEull;
-                p.pool.v[pb + q] = v;
-                p.pool.hub[pb + q] = h;
-                p.pool.dist[pb + q] = (int32_t)d;
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) {
+                kv[j] = 0;
+                if (v[j] >= 0) {
+                    kv[j] = ld<SC>(&key[v[j]]);
+                    st<SC>(&key[v[j]], KeyTraits<K>::INF);
+                }
             }
+            Append3<RELAX_ILP, int32_t> ap;
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) {
+                ap.m[0][j] = __ballot((kv[j] & 1) != 0);
+                ap.m[1][j] = ap.m[2][j] = 0;
+            }
+            if (!ap.reserve(&S.nkeep, 0, 0, 0) || pb < 0) continue;
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++)
+                if (kv[j] & 1) {
+                    const int64_t q = pb + ap.at(0, j);
+                    const uint64_t d = (uint64_t)(kv[j] >> 1);
+                    ovf |= d > 0x7FFFFFFEull;
+                    p.pool.v[q] = v[j];
+                    p.pool.hub[q] = h;
+                    p.pool.dist[q] = (int32_t)d;
+                }
         }
         if (ovf) atomicOr(p.err, ERR_BIT_OVERFLOW);
         if (HYB && tid == 0 && pb >= 0) {
@@ -635,7 +976,7 @@ enum {
     G_CNT0 = 0, G_CNT1, G_CNT2,   // near list counts, rotating by round % 3
     G_FAR, G_FAR2, G_TOUCHED,     // far list, filtered far list, touched list
     G_MIN, G_CLEAN, G_T, G_DONE, G_EARLY,
-    G_SETTLED, G_ARCS, G_NLAB, G_BASE, G_FILL, G_FARCLEAN, G_UMAX,
+    G_SETTLED, G_ARCS, G_NLAB, G_BASE, G_FILL, G_UMAX,
     G_WORDS
 };
 
@@ -649,6 +990,7 @@ template <typename K, int WG>
 __global__ __launch_bounds__(WG) void k_tree_plain(TreeParams p, int32_t h, long long* gs) {
     constexpr int SC = __HIP_MEMORY_SCOPE_AGENT;
     __shared__ PlainLds<K, WG> S;
+    __shared__ WaveQueue<K> Q[WG / 64];
     cg::grid_group grid = cg::this_grid();
     const int tid = threadIdx.x;
     const int64_t gtid = (int64_t)blockIdx.x * WG + tid;
@@ -682,17 +1024,18 @@ __global__ __launch_bounds__(WG) void k_tree_plain(TreeParams p, int32_t h, long
         const int32_t ncur = (int32_t)gs[G_CNT0 + it % 3];
         const uint32_t curbit = 1u << (it & 1), nextbit = 1u << ((it + 1) & 1);
         int32_t* cur = lists + (int64_t)(it & 1) * p.s.stride;
-        int32_t* next = lists + (int64_t)((it + 1) & 1) * p.s.stride;
         if (ncur > 0) {
+            RelaxCtx cx{};
+            cx.h = h;
+            cx.T = T;
+            cx.nextbit = nextbit;
+            cx.touched = touched;
+            cx.next = lists + (int64_t)((it + 1) & 1) * p.s.stride;
+            cx.far = far;
             for (int32_t base = blockIdx.x * WG; base < ncur; base += gridDim.x * WG)
-                relax_block<K, WG, SC>(p.g, key, flags, cur, base, min(WG, ncur - base), curbit,
-                                       nextbit, h, T, touched, next, far,
-                                       (unsigned long long*)&gs[G_TOUCHED],
-                                       (unsigned long long*)&gs[G_CNT0 + (it + 1) % 3],
-                                       (unsigned long long*)&gs[G_FAR],
-                                       (unsigned long long*)&gs[G_FARCLEAN],
-                                       (unsigned long long*)&gs[G_UMAX], nullptr, nullptr, 0u, nullptr, S.X,
-                                       arcs);
+                relax_block<K, WG, SC>(p.g, key, flags, cur, base, min(WG, ncur - base), curbit, cx,
+                                              (unsigned long long*)gs, G_TOUCHED, G_CNT0 + (it + 1) % 3, G_FAR,
+                                              (unsigned long long*)&gs[G_UMAX], S.X, &Q[tid >> 6], arcs);
             if (gtid == 0) { gs[G_CNT0 + (it + 2) % 3] = 0; gs[G_SETTLED] += ncur; }
             __threadfence();
             grid.sync();
@@ -704,7 +1047,6 @@ __global__ __launch_bounds__(WG) void k_tree_plain(TreeParams p, int32_t h, long
         unsigned long long mymin = ~0ull, myclean = 0;
         for (int64_t i = gtid; i < nfar; i += gthreads) {
             int32_t v = far[i];
-            aand<SC>(&flags[v >> 3], ~(FAR_BIT << fshift(v)));
             K kv = ld<SC>(&key[v]);
             bool keep = (int64_t)(kv >> 1) >= T;
             if (keep) {
@@ -747,7 +1089,7 @@ __global__ __launch_bounds__(WG) void k_tree_plain(TreeParams p, int32_t h, long
             int64_t q = wave_append(tonear, (unsigned long long*)&gs[G_CNT0 + it % 3]);
             if (tonear) { ncurl[q] = v; aor<SC>(&flags[v >> 3], nb << fshift(v)); }
             q = wave_append(!tonear, (unsigned long long*)&gs[G_FAR]);
-            if (!tonear) { far[q] = v; aor<SC>(&flags[v >> 3], FAR_BIT << fshift(v)); }
+            if (!tonear) far[q] = v;
         }
         __threadfence();
         grid.sync();
@@ -810,7 +1152,7 @@ enum {
     T_CNT0 = 0, T_CNT1, T_CNT2,   // near list counts, rotating by round % 3
     T_FAR, T_FAR2, T_TOUCHED,     // far list, filtered far list, touched list
     T_MIN, T_CLEAN, T_T,          // bucket-end filter results, bucket bound
-    T_SETTLED, T_ARCS, T_NLAB, T_BASE, T_FILL, T_FARCLEAN, T_UMAX,
+    T_SETTLED, T_ARCS, T_NLAB, T_BASE, T_FILL, T_UMAX,
     T_ROOT,
     T_SMIN0, T_SMIN1, T_SCL0, T_SCL1,   // round-level stop test, by round parity
     T_BAR, T_ABORT,
@@ -884,10 +1226,11 @@ __device__ __forceinline__ int team_index(int b, int G, int xcd_map) {
 }
 
 template <typename K, int WG, bool PRUNE>
-__global__ __launch_bounds__(WG) void k_tree_team(TreeParams p, int W, long long* tstate, int32_t* far2_all) {
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_tree_team(TreeParams p, int W, long long* tstate, int32_t* far2_all) {
     constexpr int SC = __HIP_MEMORY_SCOPE_AGENT;
     typedef unsigned long long ull;
     __shared__ TeamLds<K, WG> S;
+    __shared__ WaveQueue<K> Q[WG / 64];
     extern __shared__ uint32_t dh[];
     const int tid = threadIdx.x;
     const int lb = team_index(blockIdx.x, gridDim.x, p.xcd_map);
@@ -962,11 +1305,12 @@ __global__ __launch_bounds__(WG) void k_tree_team(TreeParams p, int W, long long
             const int32_t ncur = min(twl<int32_t>(tw, T_CNT0 + it % 3), n);
             const uint32_t curbit = 1u << (it & 1), nextbit = 1u << ((it + 1) & 1);
             int32_t* cur = lists + (int64_t)(it & 1) * p.s.stride;
-            int32_t* next = lists + (int64_t)((it + 1) & 1) * p.s.stride;
             if (ncur > 0) {
                 // ---- early termination between rounds (the test of the
-                //      batched form, over the whole team)
-                if (p.early_term && twl<long long>(tw, T_FARCLEAN) == 0) {
+                //      batched form, over the whole team; umax only grows,
+                //      and not before every workgroup has read it here if it
+                //      is below T, so all of them take the same branch)
+                if (p.early_term && twl<ull>(tw, T_UMAX) < (ull)T) {
                     ull mn = ~0ull, cl = 0;
                     for (int64_t i = tgtid; i < ncur; i += tthreads) {
                         const K kv = ld<SC>(&key[lget<SC>(&cur[i], n)]);
@@ -984,14 +1328,9 @@ __global__ __launch_bounds__(WG) void k_tree_team(TreeParams p, int W, long long
                     const ull smin = twl<ull>(tw, T_SMIN0 + (it & 1));
                     const ull lb = smin < (ull)T ? smin : (ull)T;
                     if (twl<ull>(tw, T_SCL0 + (it & 1)) == 0 && lb > twl<ull>(tw, T_UMAX)) {
-                        const int32_t nfar = min(twl<int32_t>(tw, T_FAR), n);
                         for (int64_t i = tgtid; i < ncur; i += tthreads) {
                             const int32_t v = lget<SC>(&cur[i], n);
                             aand<SC>(&flags[v >> 3], ~(curbit << fshift(v)));
-                        }
-                        for (int64_t i = tgtid; i < nfar; i += tthreads) {
-                            const int32_t v = lget<SC>(&far[i], n);
-                            aand<SC>(&flags[v >> 3], ~(FAR_BIT << fshift(v)));
                         }
                         early = true;
                         break;
@@ -1000,13 +1339,25 @@ __global__ __launch_bounds__(WG) void k_tree_team(TreeParams p, int W, long long
                 // the near list split evenly over the team's workgroups (a
                 // small frontier would otherwise leave most of them idle)
                 const int32_t chunk = min(WG, (ncur + W - 1) / W);
+                RelaxCtx cx{};
+                cx.h = h;
+                cx.T = T;
+                cx.nextbit = nextbit;
+                cx.touched = touched;
+                cx.next = lists + (int64_t)((it + 1) & 1) * p.s.stride;
+                cx.far = far;
+                cx.prune = prune;
+                cx.poff = p.poff;
+                cx.plab = p.plab;
+                cx.pmin = p.pmin;
+                cx.dh = dh;
+                cx.pbound = (uint32_t)p.pbound;
+                cx.dhmin = S.dhmin;
+                cx.dmaj = p.dmaj != 0;
                 for (int32_t base = trank * chunk; base < ncur; base += W * chunk)
-                    relax_block<K, WG, SC>(p.g, key, flags, cur, base, min(chunk, ncur - base), curbit,
-                                           nextbit, h, T, touched, next, far, (ull*)&tw[T_TOUCHED],
-                                           (ull*)&tw[T_CNT0 + (it + 1) % 3], (ull*)&tw[T_FAR],
-                                           (ull*)&tw[T_FARCLEAN], (ull*)&tw[T_UMAX], p.poff, p.plab,
-                                           (uint32_t)p.pbound, prune ? dh : nullptr, S.X, arcs, false,
-                                           p.pmin, S.dhmin, p.dmaj != 0);
+                    relax_block<K, WG, SC>(p.g, key, flags, cur, base, min(chunk, ncur - base), curbit, cx,
+                                                  (ull*)tw, T_TOUCHED, T_CNT0 + (it + 1) % 3, T_FAR,
+                                                  (ull*)&tw[T_UMAX], S.X, &Q[tid >> 6], arcs);
                 if (leader) {
                     tws(tw, T_CNT0 + (it + 2) % 3, 0);
                     tws(tw, T_SETTLED, twl<long long>(tw, T_SETTLED) + ncur);
@@ -1020,7 +1371,6 @@ __global__ __launch_bounds__(WG) void k_tree_team(TreeParams p, int W, long long
             ull mymin = ~0ull, myclean = 0;
             for (int64_t i = tgtid; i < nfar; i += tthreads) {
                 const int32_t v = lget<SC>(&far[i], n);
-                aand<SC>(&flags[v >> 3], ~(FAR_BIT << fshift(v)));
                 const K kv = ld<SC>(&key[v]);
                 const bool keep = (int64_t)(kv >> 1) >= T;
                 if (keep) {
@@ -1044,7 +1394,7 @@ __global__ __launch_bounds__(WG) void k_tree_team(TreeParams p, int W, long long
             if (done) { early = nkeep > 0; break; }
             if (leader) {
                 tws(tw, T_FAR, 0); tws(tw, T_FAR2, 0); tws(tw, T_CLEAN, 0); tws(tw, T_MIN, INF);
-                tws(tw, T_T, Tn); tws(tw, T_FARCLEAN, 0);
+                tws(tw, T_T, Tn);
             }
             if (!team_sync(tw, W, nb, S, p.err)) return;
             // ---- next bucket: far2 -> near list of this round, or back to far
@@ -1056,8 +1406,7 @@ __global__ __launch_bounds__(WG) void k_tree_team(TreeParams p, int W, long long
                 int64_t q = wave_append(tonear, (ull*)&tw[T_CNT0 + it % 3]);
                 if (tonear && q < n) { lput<SC>(&ncurl[q], v); aor<SC>(&flags[v >> 3], curbit << fshift(v)); }
                 q = wave_append(!tonear, (ull*)&tw[T_FAR]);
-                if (!tonear && q < n) { lput<SC>(&far[q], v); aor<SC>(&flags[v >> 3], FAR_BIT << fshift(v)); }
-                (void)wave_append(!tonear && (kv & 1), (ull*)&tw[T_FARCLEAN]);
+                if (!tonear && q < n) lput<SC>(&far[q], v);
             }
             if (!team_sync(tw, W, nb, S, p.err)) return;
         }
