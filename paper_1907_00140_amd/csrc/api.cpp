@@ -185,6 +185,10 @@ struct Build {
     const uint64_t* plab_hub = nullptr;  // the same groups in hub order, (hub << 32) | dist
     int32_t hashdh = 0;                  // main phase: root distances hashed (TreeParams::hashdh)
     int32_t pbound = 0;                  // prune with the hubs [0, pbound)
+    const LayoutArc* larc = nullptr;     // unpruned main phase in input numbering (TreeParams::larc)
+    const int64_t* lrow = nullptr;
+    const int32_t* lrank = nullptr;
+    const int32_t* lorder = nullptr;
     int32_t partner = 0;                 // combined graph of a directed build (TreeParams::partner)
     unsigned long long cursor_base = 0;  // pool entries kept before the main tree phase
     int32_t grown = 0;                   // roots [0, grown) done before the main phase
@@ -208,6 +212,9 @@ struct Build {
 // labels emitted by a pruning level above which the next level is only
 // two or four times as large (else eight times)
 constexpr unsigned long long LEVEL_LABELS_X2 = 1ull << 21;
+
+// below this the key arrays stay in the caches whatever the numbering
+constexpr int32_t LAYOUT_MIN_N = 2048;
 
 size_t slot_bytes(int32_t n, int key_bits) {
     return (size_t)n * (key_bits / 8 + 4 + 12) + (size_t)((n + 7) / 8) * 4;
@@ -287,6 +294,10 @@ TreeParams params(Build& B, const Slots& s, int64_t delta, int early, const int3
     p.novf = B.ctl32 + 5;
     p.pbound = B.pbound;
     p.partner = B.partner;
+    p.larc = B.larc;
+    p.lrow = B.lrow;
+    p.lrank = B.lrank;
+    p.lorder = B.lorder;
     p.dhg = B.dhg;
     p.rlab = B.rlab;
     // teams and groups on one XCD each: the first levels' HBM-side fetches
@@ -1208,7 +1219,11 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     int64_t* smp = A.get<int64_t>(64);
     if (!smp) return CHL_ERR_OOM;
     if (int r = sample_graph(g, order, smp, st)) return r;
-    HIPCHK(hipMemcpyAsync(hc0->c32, err, 4, hipMemcpyDeviceToHost, st));
+    // (and how close the ends of the arcs are in the input's numbering)
+    const int32_t gap = (int32_t)std::min(1e9, 4 * std::sqrt((double)n));
+    int32_t* near = B.ctl32 + 6;
+    if (launch_sample_gaps(n, g->row_ptr, g->col, gap, near, st)) return CHL_ERR_HIP;
+    HIPCHK(hipMemcpyAsync(hc0->c32, err, 20, hipMemcpyDeviceToHost, st));
     tprep.record_end();
     // 32-bit keys are exact when no simple path can reach 2^31 - 1
     B.key_bits = ((double)(n - 1) * (double)B.maxw <= 2147483646.0) ? 32 : 64;
@@ -1230,6 +1245,7 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     if (A.oom) return CHL_ERR_OOM;
     HIPCHK(hipStreamSynchronize(st));
     if (hc0->c32[0]) return CHL_ERR_INVALID_ARG;
+    const bool near_input = 2 * (int64_t)hc0->c32[3] >= hc0->c32[4] && hc0->c32[4] > 0 && n >= LAYOUT_MIN_N;
     S.prep_ms = tprep.elapsed();
     B.sig = graph_signature(g);
     A.drop(smp);
@@ -1283,6 +1299,22 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     // a large prefix: the main phase hashes each root's prefix distances in
     // LDS (more workgroups resident than with a dense prefix-size array)
     B.hashdh = B.pbound >= HASH_MIN_PREFIX ? 1 : 0;
+    // Unpruned trees of a graph whose input numbering keeps neighbours close
+    // (half the arcs within 4 sqrt(n) ids, as in a road network or a mesh,
+    // stored row by row or by region) grow in that numbering: complete builds
+    // of a 512x512 grid 478 -> 397 ms. A random numbering has 8 / sqrt(n) of
+    // its arcs that close, an R-MAT graph few more, and both stay as they are.
+    if (o.mode == CHL_MODE_BATCHED && B.pbound == 0 && near_input) {
+        if (auto* larc = A.get<LayoutArc>((size_t)B.m)) {
+            if (launch_layout_arcs(B.m, g->col, g->w, pos, larc, st)) return CHL_ERR_HIP;
+            B.larc = larc;
+            B.lrow = g->row_ptr;
+            B.lrank = pos;
+            B.lorder = order;
+        } else {
+            A.oom = false;      // no room for the copy: the trees grow by rank position
+        }
+    }
     if (int r = pick_params(A, B, g, o, st, k, wg, delta, small, tune_ms)) return r;
     if (plab_byd && !small) { B.plab = plab_byd; B.dmaj = 1; }
     S.small_trees = small ? small_capacity(B.key_bits) : 0;

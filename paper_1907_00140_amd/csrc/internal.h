@@ -64,6 +64,15 @@ struct Slots {
     int32_t* lists;       // [k][3][stride]: two near lists, one far list
 };
 
+// An arc of the graph in input numbering, with the rank position of its
+// target (the rank test of a relaxation then needs no further access).
+struct alignas(16) LayoutArc {
+    int32_t u;        // target, input id
+    uint32_t w;
+    int32_t rank;     // rank position of u
+    int32_t pad;
+};
+
 struct TreeParams {
     RGraph g;
     Slots s;
@@ -112,6 +121,13 @@ struct TreeParams {
     // range in rlab[2 * root] = first entry, rlab[2 * root + 1] = count
     uint32_t* dhg;
     int64_t* rlab;
+    // unpruned trees of the batched form grown in input numbering (NULL: by
+    // rank position): arcs, row offsets, rank position of each vertex and
+    // vertex of each rank position
+    const LayoutArc* larc;
+    const int64_t* lrow;
+    const int32_t* lrank;
+    const int32_t* lorder;
     // team and group launches: 1 = a team's workgroups are taken from one
     // XCD (workgroup b of a launch runs on XCD b % 8), 0 = consecutive ids
     int32_t xcd_map;
@@ -148,6 +164,12 @@ int launch_directed_union(int32_t n, int64_t m, const int64_t* row, const int32_
 int launch_directed_split(int32_t n, int64_t total, const int64_t* off2, int32_t* hub2, const int32_t* dist2,
                           int64_t* out_off, int32_t* out_hub, int32_t* out_dist, hipStream_t st);
 // out[64]: 16 samples x (row offset, ranking entry, neighbour, weight)
+// near[0] += sampled arcs whose ends' input ids differ by at most gap,
+// near[1] += arcs sampled (the caller has cleared both)
+int launch_sample_gaps(int32_t n, const int64_t* row_ptr, const int32_t* col, int32_t gap, int32_t* near,
+                       hipStream_t st);
+int launch_layout_arcs(int64_t m, const int32_t* col, const int32_t* w, const int32_t* pos, LayoutArc* out,
+                       hipStream_t st);
 int launch_sample_input(int32_t n, int64_t m, const int64_t* row_ptr, const int32_t* col, const int32_t* w,
                         const int32_t* order, int64_t* out, hipStream_t st);
 

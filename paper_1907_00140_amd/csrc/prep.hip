@@ -250,6 +250,49 @@ __global__ void k_sample(int32_t n, int64_t m, const int64_t* __restrict__ row, 
     }
 }
 
+constexpr int GAP_VERTICES = 1024, GAP_ARCS = 8;
+
+// One vertex per thread, GAP_ARCS of its arcs.
+__global__ __launch_bounds__(256) void k_sample_gaps(int32_t n, const int64_t* __restrict__ row,
+                                                     const int32_t* __restrict__ col, int32_t gap,
+                                                     int32_t* __restrict__ near) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int32_t v = (int32_t)((int64_t)n * i / GAP_VERTICES);
+    const int64_t b = row[v], deg = row[(int64_t)v + 1] - b;
+    const int k = (int)(deg < GAP_ARCS ? deg : GAP_ARCS);
+    int hit = 0, all = k;
+    for (int j = 0; j < k; j++) {
+        const int64_t d = (int64_t)col[b + deg * j / k] - v;
+        hit += d <= gap && -d <= gap;
+    }
+    for (int d = 32; d >= 1; d >>= 1) {
+        hit += __shfl_xor(hit, d);
+        all += __shfl_xor(all, d);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&near[0], hit);
+        atomicAdd(&near[1], all);
+    }
+}
+
+int launch_sample_gaps(int32_t n, const int64_t* row_ptr, const int32_t* col, int32_t gap, int32_t* near,
+                       hipStream_t st) {
+    hipLaunchKernelGGL(k_sample_gaps, dim3(GAP_VERTICES / 256), dim3(256), 0, st, n, row_ptr, col, gap, near);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+__global__ void k_layout_arcs(int64_t m, const int32_t* __restrict__ col, const int32_t* __restrict__ w,
+                              const int32_t* __restrict__ pos, LayoutArc* __restrict__ out) {
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x)
+        out[e] = LayoutArc{col[e], (uint32_t)w[e], pos[col[e]], 0};
+}
+
+int launch_layout_arcs(int64_t m, const int32_t* col, const int32_t* w, const int32_t* pos, LayoutArc* out,
+                       hipStream_t st) {
+    if (m > 0) hipLaunchKernelGGL(k_layout_arcs, dim3(grid_for(m, 256)), dim3(256), 0, st, m, col, w, pos, out);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 int launch_sample_input(int32_t n, int64_t m, const int64_t* row_ptr, const int32_t* col, const int32_t* w,
                         const int32_t* order, int64_t* out, hipStream_t st) {
     if (n <= 0) return -1;

@@ -381,8 +381,8 @@ __device__ __forceinline__ void settle(const RGraph& g, K* key, uint32_t* flags,
 // ctr[it_, in_, if_]: the counters of the touched, next near and far lists.
 // fmin (may be NULL): lower bound of the distances in the far list. Q: the
 // wave's queue.
-template <typename K, int WG, int SCOPE, typename C>
-__device__ __forceinline__ void relax_arcs(const RGraph& g, K* key, uint32_t* flags, const Expand<K, WG>& X,
+template <typename K, int WG, int SCOPE, bool LAY, typename C>
+__device__ __forceinline__ void relax_arcs(const RGraph& g, const LayoutArc* larc, K* key, uint32_t* flags, const Expand<K, WG>& X,
                                            int32_t nv, uint32_t wpre, uint32_t total, const RelaxCtx& cx,
                                            C* ctr, int it_, int in_, int if_, unsigned long long* umax,
                                            unsigned long long* fmin, WaveQueue<K>* Q) {
@@ -404,6 +404,7 @@ __device__ __forceinline__ void relax_arcs(const RGraph& g, K* key, uint32_t* fl
             int own[RELAX_ILP];
             uint32_t rel[RELAX_ILP];
             uint64_t a[RELAX_ILP];
+            int32_t ru[RELAX_ILP];                    // rank position of the target
 #pragma unroll
             for (int j = 0; j < RELAX_ILP; j++) own[j] = 0;
 #pragma unroll 1
@@ -426,14 +427,25 @@ __device__ __forceinline__ void relax_arcs(const RGraph& g, K* key, uint32_t* fl
 #pragma unroll
             for (int j = 0; j < RELAX_ILP; j++) {
                 const uint32_t e = eb + j * WG + lane;
-                a[j] = e < total ? g.arc[X.beg[own[j]] + (rel[j] - X.off[own[j]])] : 0;
+                const int64_t at = X.beg[own[j]] + (rel[j] - X.off[own[j]]);
+                a[j] = 0;
+                ru[j] = 0;
+                if (LAY) {
+                    if (e < total) {
+                        const LayoutArc x = larc[at];
+                        a[j] = (uint64_t)(uint32_t)x.u << 32 | x.w;
+                        ru[j] = x.rank;
+                    }
+                } else if (e < total) {
+                    a[j] = g.arc[at];
+                }
                 nk[j] = X.key[own[j]];
             }
 #pragma unroll
             for (int j = 0; j < RELAX_ILP; j++) {
                 u[j] = (int32_t)(a[j] >> 32);
                 nk[j] = pack<K>((uint64_t)(nk[j] >> 1) + (uint32_t)a[j],
-                                (uint32_t)(nk[j] & 1) & (uint32_t)(u[j] > cx.h));
+                                (uint32_t)(nk[j] & 1) & (uint32_t)((LAY ? ru[j] : u[j]) > cx.h));
             }
         }
 #pragma unroll
@@ -502,7 +514,7 @@ __device__ __forceinline__ void relax_block(const RGraph& g, K* key, uint32_t* f
     uint32_t total;
     const uint32_t wpre = expand_waves<K, WG>(X, total);
     arcs += total;
-    relax_arcs<K, WG, SCOPE, C>(g, key, flags, X, nv, wpre, total, cx, ctr, it_, in_, if_, umax, nullptr, Q);
+    relax_arcs<K, WG, SCOPE, false, C>(g, nullptr, key, flags, X, nv, wpre, total, cx, ctr, it_, in_, if_, umax, nullptr, Q);
     __syncthreads();
 }
 
@@ -606,7 +618,13 @@ __device__ __forceinline__ bool may_stop(BatchedLds<K, WG>& S, const K* key, int
 // is longer than the workgroup; a bucket's end takes one pass over the far
 // list and one barrier. The three global lists change roles: a bucket's end
 // writes what stays in the far list to the free near buffer.
-template <typename K, int WG, int PHASE, bool PRUNE, bool HS>
+//
+// LAY (unpruned trees): vertices are numbered as in the input instead of by
+// rank position (TreeParams::larc), where that keeps neighbours close. A
+// tree's keys then share cache lines with those of nearby vertices, which
+// its frontier reaches in the same few rounds, and stay in L2 meanwhile; by
+// rank position each key has a line of its own that no cache holds for long.
+template <typename K, int WG, int PHASE, bool PRUNE, bool HS, bool LAY = false>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_tree_batched(TreeParams p) {
     constexpr int SC = __HIP_MEMORY_SCOPE_WORKGROUP;
     constexpr bool HYB = PHASE == 3;
@@ -626,6 +644,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
     int32_t* cur = p.s.lists + slot * 3 * p.s.stride;
     int32_t* next = cur + p.s.stride;
     int32_t* far = next + p.s.stride;
+    const int64_t* row = LAY ? p.lrow : p.g.row;
     const int64_t delta = p.delta;
     // dh is all ones between trees: a tree sets its root's entries and
     // clears them when it is done (the global array of phase 3 is set to
@@ -660,8 +679,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
             S.dhmin = 0xFFFFFFFFu;
             if (r >= 0) {
                 // the root, with key (0, clean), is the near list of round 0
-                S.nl[0][0] = r;
-                touched[0] = r;
+                const int32_t v = LAY ? p.lorder[r] : r;
+                S.nl[0][0] = v;
+                touched[0] = v;
                 for (int i = 0; i < B_CTRS; i++) S.ctr[i] = 0;
                 S.ctr[B_TOUCHED] = 1;
                 S.be[0] = S.be[1] = BucketEnd{0, 0, 0, ~0ull};
@@ -682,7 +702,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
             __syncthreads();
             continue;
         }
-        if (tid == 0) st<SC>(&key[h], pack<K>(0, 1));
+        if (tid == 0) st<SC>(&key[S.nl[0][0]], pack<K>(0, 1));
         if (prune) {
             for (int64_t i = p.poff[hg] + tid; i < p.poff[hg + 1]; i += WG) {
                 const uint64_t lx = p.plab[i];
@@ -762,8 +782,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                             aand<SC>(&flags[v >> 3], ~(curbit << fshift(v)));
                             kv = ld<SC>(&key[v]);
                         }
-                        const int64_t b = p.g.row[v];
-                        deg = (uint32_t)(p.g.row[v + 1] - b);
+                        const int64_t b = row[v];
+                        deg = (uint32_t)(row[v + 1] - b);
                         S.X.beg[tid] = b;
                         S.X.key[tid] = kv;
                         mn = (ull)(kv >> 1);
@@ -794,9 +814,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         if (cl == 0 && mn > um) { stopped = true; break; }
                     }
                     arcs += total;
-                    relax_arcs<K, WG, SC, int32_t>(p.g, key, flags, S.X, nv, wpre, total, cx, S.ctr,
-                                                          B_TOUCHED, B_NEXT + (it + 1) % 3, B_FAR, &S.umax,
-                                                          &S.fmin, &Q[w]);
+                    relax_arcs<K, WG, SC, LAY, int32_t>(p.g, p.larc, key, flags, S.X, nv, wpre, total, cx, S.ctr,
+                                                        B_TOUCHED, B_NEXT + (it + 1) % 3, B_FAR, &S.umax,
+                                                        &S.fmin, &Q[w]);
                     if (base + WG < ncur) __syncthreads();      // X is used again
                 }
                 if (stopped) { settled -= ncur; break; }
@@ -941,7 +961,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                     const int64_t q = pb + ap.at(0, j);
                     const uint64_t d = (uint64_t)(kv[j] >> 1);
                     ovf |= d > 0x7FFFFFFEull;
-                    p.pool.v[q] = v[j];
+                    p.pool.v[q] = LAY ? p.lrank[v[j]] : v[j];
                     p.pool.hub[q] = h;
                     p.pool.dist[q] = (int32_t)d;
                 }
@@ -2426,11 +2446,13 @@ int launch_batched_t(const TreeParams& p, int phase, hipStream_t st) {
         hipLaunchKernelGGL((k_tree_batched<K, WG, 3, true, false>), g, b, 0, st, p);
     } else if (phase == 1 && hs) hipLaunchKernelGGL((k_tree_batched<K, WG, 1, true, true>), g, b, 0, st, p);
     else if (phase == 1 && pr) hipLaunchKernelGGL((k_tree_batched<K, WG, 1, true, false>), g, b, dl, st, p);
+    else if (phase == 1 && p.larc) hipLaunchKernelGGL((k_tree_batched<K, WG, 1, false, false, true>), g, b, 0, st, p);
     else if (phase == 1) hipLaunchKernelGGL((k_tree_batched<K, WG, 1, false, false>), g, b, 0, st, p);
     else if (phase == 2 && pr) hipLaunchKernelGGL((k_tree_batched<K, WG, 2, true, false>), g, b, dl, st, p);
     else if (phase == 2) hipLaunchKernelGGL((k_tree_batched<K, WG, 2, false, false>), g, b, 0, st, p);
     else if (hs) hipLaunchKernelGGL((k_tree_batched<K, WG, 0, true, true>), g, b, 0, st, p);
     else if (pr) hipLaunchKernelGGL((k_tree_batched<K, WG, 0, true, false>), g, b, dl, st, p);
+    else if (p.larc) hipLaunchKernelGGL((k_tree_batched<K, WG, 0, false, false, true>), g, b, 0, st, p);
     else hipLaunchKernelGGL((k_tree_batched<K, WG, 0, false, false>), g, b, 0, st, p);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

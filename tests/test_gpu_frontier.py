@@ -45,3 +45,37 @@ def test_near_list_sizes(wg, width):
         L, off, hub, dist = gpu_labels(row, col, w, order, wg_size=wg, roots_in_flight=7, autotune=False, **kw)
         assert_same_labels(off, hub, dist, ref, str((wg, width, kw)))
         L.free()
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 2047), (2, 1024), (45, 46), (53, 61), (128, 17)])
+@pytest.mark.parametrize("directed", [False, True])
+def test_input_numbering(rows, cols, directed):
+    """Unpruned trees of a graph stored row by row grow in input numbering
+    (from 2048 vertices on, half the arcs within 4 sqrt(n) ids); the same
+    graph with scrambled ids grows by rank position. Complete builds and root
+    subsets, in both forms, against the oracle."""
+    print("input numbering", rows, cols, directed, flush=True)
+    n, u, v, w = gg.grid_edges(rows, cols, 1, 4, 5, diag_prob=0.3)
+    g = np.random.default_rng(rows)
+    for ids in (np.arange(n), g.permutation(n)):
+        e = list(zip(ids[u].tolist(), ids[v].tolist(), w.tolist()))
+        row, col, ww = pins.csr_from_edges(n, e)
+        order = gg.random_rank(n, 3)
+        if directed:
+            refs = oracle.chl_directed(row, col, ww, order)
+        else:
+            refs = [oracle.chl(row, col, ww, order)]
+        for kw in (dict(delta=1), dict(delta=7, wg_size=64, roots_in_flight=300), dict(early_term=False, delta=50)):
+            L, off, hub, dist = gpu_labels(row, col, ww, order, autotune=False, prune_hubs=-1, directed=directed, **kw)
+            assert_same_labels(off, hub, dist, refs[0], str((rows, cols, kw)))
+            if directed:
+                off, hub, dist = (x.numpy() for x in L.export_in("cpu"))
+                assert_same_labels(off, hub, dist, refs[1], str((rows, cols, kw)))
+            L.free()
+        if not directed:
+            roots = (5, 40, n // 41)
+            L, off, hub, dist = gpu_labels(row, col, ww, order, autotune=False, prune_hubs=-1, roots=roots)
+            want = np.isin(refs[0].hub_pos, roots[0] + roots[2] * np.arange(roots[1]))
+            assert np.array_equal(hub, refs[0].hub_pos[want])
+            assert np.array_equal(dist.astype(np.int64), refs[0].dist[want])
+            L.free()
