@@ -180,9 +180,8 @@ struct Build {
     // rank-prefix pruning: labels found so far, grouped by rank position
     const int64_t* poff = nullptr;
     const uint64_t* plab = nullptr;
-    uint32_t* pmin = nullptr;            // lower bound of each vertex's group distances
-    int32_t dmaj = 0;                    // plab entries (dist << 32) | hub, groups by distance (TreeParams::dmaj)
-    const uint64_t* plab_hub = nullptr;  // the same groups in hub order, (hub << 32) | dist
+    uint64_t* head = nullptr;            // first entries of each group (TreeParams::head)
+    const uint64_t* plab_hub = nullptr;  // the same groups as (hub << 32) | dist
     int32_t hashdh = 0;                  // main phase: root distances hashed (TreeParams::hashdh)
     int32_t pbound = 0;                  // prune with the hubs [0, pbound)
     const LayoutArc* larc = nullptr;     // unpruned main phase in input numbering (TreeParams::larc)
@@ -287,8 +286,8 @@ TreeParams params(Build& B, const Slots& s, int64_t delta, int early, const int3
     p.pop_batch = std::max(1, std::min(16, nroots / std::max(1, 8 * s.k)));
     p.poff = B.poff;
     p.plab = B.plab;
-    p.pmin = B.pmin;
-    p.dmaj = B.dmaj;
+    p.head = B.head;
+    p.plab_hub = B.plab_hub;
     p.hashdh = B.hashdh;
     p.ovf = B.far2;
     p.novf = B.ctl32 + 5;
@@ -716,9 +715,8 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
     int32_t* pcount = A.get<int32_t>(n);
     int32_t* pfill = A.get<int32_t>(n);
     int64_t* poff[2] = {A.get<int64_t>((size_t)n + 1), A.get<int64_t>((size_t)n + 1)};
-    B.pmin = A.get<uint32_t>(n);
+    B.head = A.get<uint64_t>((size_t)n * PRUNE_HEAD);
     if (A.oom) return CHL_ERR_OOM;
-    HIPCHK(hipMemsetAsync(B.pmin, 0xFF, (size_t)n * 4, st));
     uint64_t* plab[2] = {nullptr, nullptr};
     size_t plab_cap[2] = {0, 0};
     uint64_t* byd = nullptr;            // the groups ordered by distance
@@ -744,15 +742,12 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
             if (!plab[nx]) return CHL_ERR_OOM;
         }
         if (launch_prefix_extend(n, B.pool, grouped, used, pcount, cur < 0 ? nullptr : poff[cur],
-                                 cur < 0 ? nullptr : plab[cur], poff[nx], plab[nx], pfill, scan_tmp, st) ||
-            launch_group_min(B.pool, grouped, used, B.pmin, st))
+                                 cur < 0 ? nullptr : plab[cur], poff[nx], plab[nx], pfill, scan_tmp, st))
             return CHL_ERR_HIP;
         cur = nx;
         grouped = used;
         B.poff = poff[cur];
-        B.plab = plab[cur];
         B.plab_hub = plab[cur];
-        B.dmaj = 0;
         B.cursor_base = used;
         // the kernels read the groups ordered by distance (a pruning test
         // stops at the first entry that cannot give a shorter walk); the
@@ -764,10 +759,10 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
             if (!byd) return CHL_ERR_OOM;
         }
         if (launch_swap_halves(plab[cur], byd, used, st) ||
-            launch_segsort_u64(byd, poff[cur], n, (int64_t)used, nullptr, st))
+            launch_segsort_u64(byd, poff[cur], n, (int64_t)used, nullptr, st) ||
+            launch_group_heads(n, poff[cur], byd, B.head, st))
             return CHL_ERR_HIP;
         B.plab = byd;
-        B.dmaj = 1;
         return 0;
     };
     // level 0
@@ -1053,14 +1048,10 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
     // [0, B.cursor_base)) and the PLaNT windows' entries after them
     unsigned long long grouped = B.last_used;
     const unsigned long long lev = B.poff ? B.cursor_base : 0;
-    if (int r = extend(B.poff, B.dmaj ? B.plab_hub : B.plab, lev, grouped, 0)) return r;
-    if (!B.pmin) {
-        B.pmin = A.get<uint32_t>(n);
-        if (!B.pmin) return CHL_ERR_OOM;
-        HIPCHK(hipMemsetAsync(B.pmin, 0xFF, (size_t)n * 4, st));
-        if (launch_group_min(B.pool, 0, grouped, B.pmin, st)) return CHL_ERR_HIP;
-    } else if (launch_group_min(B.pool, lev, grouped, B.pmin, st)) {
-        return CHL_ERR_HIP;
+    if (int r = extend(B.poff, B.plab_hub, lev, grouped, 0)) return r;
+    if (!B.head) {
+        B.head = A.get<uint64_t>((size_t)n * PRUNE_HEAD);
+        if (!B.head) return CHL_ERR_OOM;
     }
     int cur = 0;
     int64_t x = std::max<int64_t>(64, 2 * (int64_t)s.k);
@@ -1079,11 +1070,11 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
             if (!byd) return CHL_ERR_OOM;
         }
         if (launch_swap_halves(tlab[cur], byd, grouped, st) ||
-            launch_segsort_u64(byd, toff[cur], n, (int64_t)grouped, nullptr, st))
+            launch_segsort_u64(byd, toff[cur], n, (int64_t)grouped, nullptr, st) ||
+            launch_group_heads(n, toff[cur], byd, B.head, st))
             return CHL_ERR_HIP;
         B.poff = toff[cur];
         B.plab = byd;
-        B.dmaj = 1;
         B.pbound = lo;
         if (int r = run_batched(A, B, s, wg, delta, o.early_term, nullptr, hi - lo, st, launches, 3, lo)) return r;
         const unsigned long long used = B.last_used;
@@ -1119,7 +1110,6 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
         HIPCHK(hipMemcpyAsync(B.ctl64, &end, 8, hipMemcpyHostToDevice, st));
         // the groups again, from the kept labels only
         if (int r = extend(toff[cur], tlab[cur], grouped, end, nx)) return r;
-        if (launch_group_min(B.pool, grouped, end, B.pmin, st)) return CHL_ERR_HIP;
         clean_ms += tc.stop();
         A.drop(keep);
         A.drop(pos);
@@ -1138,8 +1128,7 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
     B.dhg = nullptr;
     B.rlab = nullptr;
     B.poff = toff[cur];
-    B.plab = tlab[cur];
-    B.dmaj = 0;
+    B.plab_hub = tlab[cur];
     if (own_stats) { A.drop(own_stats); B.stats = nullptr; }
     return 0;
 }
@@ -1288,14 +1277,6 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     int64_t delta = 0;
     double tune_ms = 0;
     bool small = false;
-    // The pruning levels leave the groups ordered by distance (B.dmaj), as
-    // the batched, team and group kernels read them: a candidate's pruning
-    // test stops at the first entry whose distance, plus the root's nearest
-    // prefix hub, exceeds the candidate (no later entry can give a shorter
-    // walk). R-MAT 20: main phase 41.4 -> 32.7 ms. The small-tree kernel
-    // reads the groups in hub order, and so does the tuner's probe of it.
-    const uint64_t* plab_byd = B.dmaj ? B.plab : nullptr;
-    if (B.dmaj) { B.plab = B.plab_hub; B.dmaj = 0; }
     // a large prefix: the main phase hashes each root's prefix distances in
     // LDS (more workgroups resident than with a dense prefix-size array)
     B.hashdh = B.pbound >= HASH_MIN_PREFIX ? 1 : 0;
@@ -1316,7 +1297,6 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
         }
     }
     if (int r = pick_params(A, B, g, o, st, k, wg, delta, small, tune_ms)) return r;
-    if (plab_byd && !small) { B.plab = plab_byd; B.dmaj = 1; }
     S.small_trees = small ? small_capacity(B.key_bits) : 0;
     S.tune_ms = tune_ms;
     S.roots_in_flight = k;

@@ -227,17 +227,18 @@ int launch_level_order(const int64_t* poff, int32_t g, int32_t g2, int32_t partn
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-__global__ void k_group_min(const int32_t* __restrict__ pv, const int32_t* __restrict__ pd, uint64_t cnt,
-                            uint32_t* __restrict__ pmin) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt;
-         i += (uint64_t)gridDim.x * blockDim.x)
-        atomicMin(&pmin[pv[i]], (uint32_t)pd[i]);
+__global__ void k_group_heads(int32_t n, const int64_t* __restrict__ off, const uint64_t* __restrict__ lab,
+                              uint64_t* __restrict__ head) {
+    const int64_t total = (int64_t)n * PRUNE_HEAD;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t v = i / PRUNE_HEAD, e = off[v] + i % PRUNE_HEAD;
+        head[i] = e < off[v + 1] ? lab[e] : ~0ull;
+    }
 }
 
-int launch_group_min(const Pool& pool, uint64_t from, uint64_t to, uint32_t* pmin, hipStream_t st) {
-    if (to <= from) return 0;
-    hipLaunchKernelGGL(k_group_min, dim3(g(to - from)), dim3(256), 0, st, pool.v + from, pool.dist + from, to - from,
-                       pmin);
+int launch_group_heads(int32_t n, const int64_t* off, const uint64_t* lab, uint64_t* head, hipStream_t st) {
+    hipLaunchKernelGGL(k_group_heads, dim3(g((uint64_t)n * PRUNE_HEAD)), dim3(256), 0, st, n, off, lab, head);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

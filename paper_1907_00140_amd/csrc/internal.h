@@ -90,19 +90,17 @@ struct TreeParams {
     int32_t root_base;      // batched form without a root list: root = root_base + counter
     int32_t pop_batch;      // batched form: queue positions taken per atomic (>= 1)
     // rank-prefix pruning: the labels found so far, grouped by vertex (rank
-    // position), plab[poff[v] .. poff[v+1]) = (hub << 32) | dist;
-    // trees of roots >= pbound prune with the hubs [0, pbound) (their labels
-    // are complete); poff == NULL or pbound == 0 disables pruning
+    // position), plab[poff[v] .. poff[v+1]) = (dist << 32) | hub, each group
+    // sorted by distance; head[v * PRUNE_HEAD ..): the group's first entries
+    // (all ones where it is shorter); plab_hub: the groups as (hub << 32) |
+    // dist in no particular order (small-tree kernel). Trees of roots >=
+    // pbound prune with the hubs [0, pbound) (their labels are complete);
+    // poff == NULL or pbound == 0 disables pruning
     const int64_t* poff;
     const uint64_t* plab;
+    const uint64_t* head;
+    const uint64_t* plab_hub;
     int32_t pbound;
-    // pmin[v] <= every distance in v's group (NULL: none): a walk through a
-    // prefix hub from root h to v is at least (h's smallest prefix distance)
-    // + pmin[v], so a candidate below that bound skips reading v's group
-    const uint32_t* pmin;
-    // 1: plab entries are (dist << 32) | hub and each group is sorted by
-    // distance (the batched kernel's main phase); 0: (hub << 32) | dist
-    int32_t dmaj;
     // batched form, main phase and its probes: 1 = the root's prefix
     // distances in a small LDS hash instead of a dense LDS array (more
     // workgroups resident); a root with more than HASH_MAX_LABELS prefix
@@ -233,10 +231,9 @@ int launch_assemble(int32_t n, const int32_t* order, const Pool& pool, uint64_t 
 int launch_prefix_extend(int32_t n, const Pool& pool, uint64_t from, uint64_t used, int32_t* count,
                          const int64_t* off_old, const uint64_t* lab_old, int64_t* off_new, uint64_t* lab_new,
                          int32_t* fill, void* scan_temp, hipStream_t st);
-// assemble.hip: pmin[v] = min(pmin[v], distance) over the pool entries
-// [from, to) of v (pmin starts all ones and only decreases, so it stays a
-// lower bound of v's group when entries leave it)
-int launch_group_min(const Pool& pool, uint64_t from, uint64_t to, uint32_t* pmin, hipStream_t st);
+// assemble.hip: head[v * PRUNE_HEAD + z] = entry z of v's group (all ones
+// beyond its end)
+int launch_group_heads(int32_t n, const int64_t* off, const uint64_t* lab, uint64_t* head, hipStream_t st);
 // assemble.hip: out[i] = in[i] with its two 32-bit halves exchanged
 int launch_swap_halves(const uint64_t* in, uint64_t* out, uint64_t total, hipStream_t st);
 // assemble.hip: count[v] = size of v's group in off (0 for every v when
@@ -276,6 +273,7 @@ int launch_level_order(const int64_t* poff, int32_t g, int32_t g2, int32_t partn
 // assemble.hip: totals of the per-root statistics (settled, arcs, stopped
 // early) into sums[0..2] (zeroed by the caller)
 int launch_stat_sums(int32_t n, const int64_t* stats, int64_t* sums, hipStream_t st);
+constexpr int PRUNE_HEAD = 4;          // prefix labels of a vertex that are tested first (32 bytes)
 constexpr int HASH_MIN_PREFIX = 4096;   // prefixes from this size hash the root's distances
 constexpr int HASH_MAX_LABELS = 512;    // prefix labels of a root that the hash holds
 constexpr int MAX_PREFIX = 8192;   // largest pruning prefix (root distances live in LDS, 32 KB)

@@ -94,34 +94,6 @@ __device__ __forceinline__ int32_t lget(const int32_t* p, int32_t n) {
 template <int SCOPE>
 __device__ __forceinline__ void lput(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, SCOPE); }
 
-// Block-wide exclusive scan of uint32 (WG threads). wsum: WG/64 entries of LDS.
-template <int WG>
-__device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t* wsum, uint32_t& total) {
-    constexpr int NW = WG / 64;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t v = x;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t y = __shfl_up(v, d);
-        if (lane >= d) v += y;
-    }
-    if (lane == 63) wsum[w] = v;
-    __syncthreads();
-    if (w == 0) {
-        uint32_t s = lane < NW ? wsum[lane] : 0u;
-#pragma unroll
-        for (int d = 1; d < NW; d <<= 1) {
-            uint32_t y = __shfl_up(s, d);
-            if (lane >= d) s += y;
-        }
-        if (lane < NW) wsum[lane] = s;
-    }
-    __syncthreads();
-    total = wsum[NW - 1];
-    uint32_t ex = (w ? wsum[w - 1] : 0u) + v - x;
-    return ex;
-}
-
 template <int WG, typename T, typename F>
 __device__ __forceinline__ T block_reduce(T x, T* red, T ident, F op) {
     constexpr int NW = WG / 64;
@@ -193,16 +165,19 @@ struct HashLds {
     uint32_t v[C];
 };
 
-// Candidates of a wave: the arcs whose new distance is below the key seen at
-// their target. They are a minority of the arcs, and the pruning test's
-// length differs from one to the next, so they are gathered here and tested
-// and applied 64 at a time, one per lane, instead of each thread taking its
-// own few one after the other with most lanes idle.
+// Candidates of a wave: the arcs that may improve their target. They are a
+// minority of the arcs, and what is left to do for them differs from one to
+// the next, so they are gathered here and tested and applied 64 at a time,
+// one per lane, instead of each thread taking its own few one after the other
+// with most lanes idle. Unpruned trees queue the arcs whose new distance is
+// below the key seen at the target; pruned ones those that the target's first
+// prefix labels do not prune (MORE_BIT of u: later ones still may).
 template <typename K>
 struct WaveQueue {
     K nk[64 * (RELAX_ILP + 1)];
-    int32_t u[64 * (RELAX_ILP + 1)];
+    uint32_t u[64 * (RELAX_ILP + 1)];
 };
+constexpr uint32_t MORE_BIT = 1u << 31;
 
 // LDS written by some lanes of a wave and read by others: order the wave's
 // accesses (a wave executes in lockstep; this keeps the compiler from moving
@@ -229,19 +204,81 @@ struct RelaxCtx {
     bool prune;
     const int64_t* poff;
     const uint64_t* plab;
-    const uint32_t* pmin;
+    const uint64_t* head;
     const uint32_t* dh;
     const int32_t* hk;        // hashed root distances (keys), or NULL
     uint32_t pbound;
     uint32_t dhmin;
-    bool dmaj;
     bool rank_query;
 };
 
+// Rank-prefix pruning (Section 4.3). The labels of the hubs [0, pbound),
+// complete because their trees are done, give the length of the shortest
+// root-u walk through each of them: the root's distance d(h, x), held in LDS,
+// plus u's label (x, d(x, u)). If one is no longer than a candidate's
+// distance nd, the candidate is either not a shortest path or a shortest path
+// through a hub that outranks the root; either way it cannot lead to a label,
+// and a vertex whose true key is clean never has such a hub on its shortest
+// paths, so dropping the candidate changes no label. u's labels come nearest
+// hub first: once one is too far with the root's nearest hub (dhmin), so are
+// the rest. In a pruned tree most arcs lead to vertices that no key marks,
+// because the test drops them each time (R-MAT 20: 75% of the arcs pass the
+// key comparison, and of those 58% are pruned by u's nearest hub, 77% by the
+// two nearest, 89% by four), so the first PRUNE_HEAD labels sit beside each
+// other in one 32-byte sector (head[u * PRUNE_HEAD], all ones beyond the last
+// label) and are tested before the key is read at all: one access to an
+// array that all trees share instead of key, bound, offsets and labels one
+// after the other. R-MAT 20 levels, before and after (ms): team [16,32) 9.2 ->
+// 4.5, groups [32,128) 36.6 -> 14.6 and [128,256) 25.8 -> 11.7, wide [256,1024)
+// 45.4 -> 19.7; the build 177 -> 113. pruned: the head decides; more: labels beyond it may.
+template <typename LOOK>
+__device__ __forceinline__ void head_test(const uint64_t (&e)[PRUNE_HEAD], uint64_t nd, uint32_t pbound,
+                                          uint32_t dhmin, LOOK look, bool& pruned, bool& more) {
+    pruned = false;
+#pragma unroll
+    for (int z = 0; z < PRUNE_HEAD; z++) {
+        const uint32_t x = (uint32_t)e[z];
+        const uint32_t da = x < pbound ? look(x) : 0xFFFFFFFFu;
+        pruned |= da != 0xFFFFFFFFu && (uint64_t)da + (uint32_t)(e[z] >> 32) <= nd;
+    }
+    more = !pruned && e[PRUNE_HEAD - 1] != ~0ull && (uint64_t)(uint32_t)(e[PRUNE_HEAD - 1] >> 32) + dhmin <= nd;
+}
+
+// Do u's prefix labels beyond its head prune a candidate?
+template <typename LOOK>
+__device__ __forceinline__ bool tail_test(const int64_t* poff, const uint64_t* plab, int32_t u, uint64_t nd,
+                                          uint32_t pbound, uint32_t dhmin, LOOK look) {
+    int64_t i = poff[u] + PRUNE_HEAD;
+    const int64_t le = poff[u + 1];
+    bool pruned = false;
+#pragma unroll 1
+    for (; i < le && !pruned; i += 8) {
+        uint64_t lx[8];
+#pragma unroll
+        for (int z = 0; z < 8; z++) lx[z] = i + z < le ? plab[i + z] : ~0ull;
+#pragma unroll
+        for (int z = 0; z < 8; z++) {
+            const uint32_t x = (uint32_t)lx[z];
+            if (x >= pbound) continue;
+            const uint32_t da = look(x);
+            if (da != 0xFFFFFFFFu && (uint64_t)da + (uint32_t)(lx[z] >> 32) <= nd) pruned = true;
+        }
+        if ((uint64_t)(uint32_t)(lx[7] >> 32) + dhmin > nd) break;
+    }
+    return pruned;
+}
+
+__device__ __forceinline__ void load_head(const uint64_t* head, int32_t u, uint64_t (&e)[PRUNE_HEAD]) {
+    static_assert(PRUNE_HEAD == 4, "two 16-byte loads");
+    const ulonglong2* q = (const ulonglong2*)(head + (int64_t)u * PRUNE_HEAD);
+    const ulonglong2 a = q[0], b = q[1];
+    e[0] = a.x; e[1] = a.y; e[2] = b.x; e[3] = b.y;
+}
+
 // The part of a chunk's expansion before its first barrier: the degree scan
 // within the wave. deg = 0 beyond the chunk.
-template <typename K, int WG>
-__device__ __forceinline__ void expand_scan(Expand<K, WG>& X, uint32_t deg) {
+template <typename E>
+__device__ __forceinline__ void expand_scan(E& X, uint32_t deg) {
     const int tid = threadIdx.x, lane = tid & 63;
     uint32_t inc = deg;
 #pragma unroll
@@ -255,8 +292,8 @@ __device__ __forceinline__ void expand_scan(Expand<K, WG>& X, uint32_t deg) {
 
 // Behind that barrier: arcs before each wave's vertices (lane i of the
 // result: wave i; the total beyond the last wave).
-template <typename K, int WG>
-__device__ __forceinline__ uint32_t expand_waves(const Expand<K, WG>& X, uint32_t& total) {
+template <int WG, typename E>
+__device__ __forceinline__ uint32_t expand_waves(const E& X, uint32_t& total) {
     constexpr int NW = WG / 64;
     const int lane = threadIdx.x & 63;
     const uint32_t x = lane < NW ? X.wtot[lane] : 0u;
@@ -303,50 +340,25 @@ struct Append3 {
 
 // Test and apply nc candidates of a wave's queue, one per lane. ctr[it_, in_,
 // if_]: the counters of the touched, next near and far lists.
-template <typename K, int SCOPE, typename C>
+template <typename K, int SCOPE, bool PRUNE, typename C>
 __device__ __forceinline__ void settle(const RGraph& g, K* key, uint32_t* flags, const WaveQueue<K>* Q, int first,
                                        int nc, const RelaxCtx& cx, C* ctr, int it_, int in_, int if_,
                                        unsigned long long& my_umax, unsigned long long& my_fmin) {
     typedef unsigned long long ull;
     const int lane = threadIdx.x & 63;
     bool cand = lane < nc;
-    int32_t u = 0;
+    uint32_t qu = 0;
     K nk = 0;
-    if (cand) { u = Q->u[first + lane]; nk = Q->nk[first + lane]; }
+    if (cand) { qu = Q->u[first + lane]; nk = Q->nk[first + lane]; }
+    const int32_t u = (int32_t)(qu & ~MORE_BIT);
     const uint64_t nd = (uint64_t)(nk >> 1);
-    if (cx.prune) {
-        // Rank-prefix pruning (Section 4.3): the labels of the hubs
-        // [0, pbound), complete because their trees are done, give the
-        // length of the shortest root-u walk through each of them (dh holds
-        // the root's side). If one is no longer than the candidate, the
-        // candidate is either not a shortest path or a shortest path through
-        // a hub that outranks the root; either way it cannot lead to a label,
-        // and a vertex whose true key is clean never has such a hub on its
-        // shortest paths, so dropping the candidate changes no label. No walk
-        // through a prefix hub is shorter than the root's nearest prefix hub
-        // plus u's: below that bound u's group is not read.
-        int64_t i = 0, le = 0;
-        if (cand && (uint64_t)cx.dhmin + (cx.pmin ? cx.pmin[u] : 0u) <= nd) {
-            i = cx.poff[u];
-            le = cx.poff[u + 1];
-        }
-        // u's entries are read 8 at a time until one prunes
-#pragma unroll 1
-        for (; i < le && cand; i += 8) {
-            uint64_t lx[8];
-#pragma unroll
-            for (int z = 0; z < 8; z++) lx[z] = i + z < le ? cx.plab[i + z] : ~0ull;
-#pragma unroll
-            for (int z = 0; z < 8; z++) {
-                const uint32_t x = cx.dmaj ? (uint32_t)lx[z] : (uint32_t)(lx[z] >> 32);
-                const uint32_t dd = cx.dmaj ? (uint32_t)(lx[z] >> 32) : (uint32_t)lx[z];
-                if (x >= cx.pbound) continue;
-                const uint32_t da = cx.hk ? hash_lookup(cx.hk, cx.dh, x) : cx.dh[x];
-                if (da != 0xFFFFFFFFu && (uint64_t)da + dd <= nd) cand = false;
-            }
-            // groups ordered by distance: no later entry is closer
-            if (cx.dmaj && (uint64_t)(uint32_t)(lx[7] >> 32) + cx.dhmin > nd) break;
-        }
+    if constexpr (PRUNE) {
+        // keys only decrease: a candidate that is not below the value read
+        // here would not win the atomic either
+        if (cand) cand = nk < ld<SCOPE>(&key[u]);
+        if (cand && (qu & MORE_BIT))
+            cand = !tail_test(cx.poff, cx.plab, u, nd, cx.pbound, cx.dhmin,
+                              [&](uint32_t x) { return cx.hk ? hash_lookup(cx.hk, cx.dh, x) : cx.dh[x]; });
     }
     K old = 0;
     if (cand) old = amin<SCOPE>(&key[u], nk);
@@ -381,7 +393,7 @@ __device__ __forceinline__ void settle(const RGraph& g, K* key, uint32_t* flags,
 // ctr[it_, in_, if_]: the counters of the touched, next near and far lists.
 // fmin (may be NULL): lower bound of the distances in the far list. Q: the
 // wave's queue.
-template <typename K, int WG, int SCOPE, bool LAY, typename C>
+template <typename K, int WG, int SCOPE, bool PRUNE, bool LAY, typename C>
 __device__ __forceinline__ void relax_arcs(const RGraph& g, const LayoutArc* larc, K* key, uint32_t* flags, const Expand<K, WG>& X,
                                            int32_t nv, uint32_t wpre, uint32_t total, const RelaxCtx& cx,
                                            C* ctr, int it_, int in_, int if_, unsigned long long* umax,
@@ -398,7 +410,7 @@ __device__ __forceinline__ void relax_arcs(const RGraph& g, const LayoutArc* lar
 #pragma unroll 1
     for (uint32_t eb = (uint32_t)(tid & ~63); eb < total; eb += WG * RELAX_ILP) {
         int32_t u[RELAX_ILP];
-        K nk[RELAX_ILP], old[RELAX_ILP];
+        K nk[RELAX_ILP];
         bool cand[RELAX_ILP];
         {
             int own[RELAX_ILP];
@@ -448,35 +460,50 @@ __device__ __forceinline__ void relax_arcs(const RGraph& g, const LayoutArc* lar
                                 (uint32_t)(nk[j] & 1) & (uint32_t)((LAY ? ru[j] : u[j]) > cx.h));
             }
         }
+        if constexpr (PRUNE) {
+            uint64_t e4[RELAX_ILP][PRUNE_HEAD];
 #pragma unroll
-        for (int j = 0; j < RELAX_ILP; j++) {
-            const uint32_t e = eb + j * WG + lane;
-            old[j] = e < total ? ld<SCOPE>(&key[u[j]]) : (K)0;
-        }
+            for (int j = 0; j < RELAX_ILP; j++) load_head(cx.head, u[j], e4[j]);   // (vertex 0 beyond the last arc)
 #pragma unroll
-        for (int j = 0; j < RELAX_ILP; j++) {
+            for (int j = 0; j < RELAX_ILP; j++) {
+                bool pruned = false, more = false;
+                if (cx.prune)
+                    head_test(e4[j], (uint64_t)(nk[j] >> 1), cx.pbound, cx.dhmin,
+                              [&](uint32_t x) { return cx.hk ? hash_lookup(cx.hk, cx.dh, x) : cx.dh[x]; }, pruned,
+                              more);
+                cand[j] = eb + j * WG + lane < total && !pruned;
+                // rank query of the pruned construction (Algorithm 1): a vertex
+                // that outranks the root is neither labelled nor expanded
+                if (cx.rank_query && u[j] < cx.h) cand[j] = false;
+                if (more) u[j] |= (int32_t)MORE_BIT;
+            }
+        } else {
+            K old[RELAX_ILP];
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) {
+                const uint32_t e = eb + j * WG + lane;
+                old[j] = e < total ? ld<SCOPE>(&key[u[j]]) : (K)0;
+            }
             // Keys only decrease, so a value read earlier is never below the
             // current one: when the candidate is not below it, the atomic
             // would fail and is skipped. (Beyond the last arc the key read is 0.)
-            cand[j] = nk[j] < old[j];
-            // rank query of the pruned construction (Algorithm 1): a vertex
-            // that outranks the root is neither labelled nor expanded
-            if (cx.rank_query && u[j] < cx.h) cand[j] = false;
+#pragma unroll
+            for (int j = 0; j < RELAX_ILP; j++) cand[j] = nk[j] < old[j];
         }
 #pragma unroll
         for (int j = 0; j < RELAX_ILP; j++) {
             const uint64_t m = __ballot(cand[j]);
             const int q = nq + (int)lanes_below(m);
-            if (cand[j]) { Q->nk[q] = nk[j]; Q->u[q] = u[j]; }
+            if (cand[j]) { Q->nk[q] = nk[j]; Q->u[q] = (uint32_t)u[j]; }
             nq += (int)__popcll(m);
         }
         wave_sync();
 #pragma unroll 1
         for (; nq >= 64; nq -= 64)
-            settle<K, SCOPE, C>(g, key, flags, Q, nq - 64, 64, cx, ctr, it_, in_, if_, my_umax, my_fmin);
+            settle<K, SCOPE, PRUNE, C>(g, key, flags, Q, nq - 64, 64, cx, ctr, it_, in_, if_, my_umax, my_fmin);
         wave_sync();
     }
-    if (nq > 0) settle<K, SCOPE, C>(g, key, flags, Q, 0, nq, cx, ctr, it_, in_, if_, my_umax, my_fmin);
+    if (nq > 0) settle<K, SCOPE, PRUNE, C>(g, key, flags, Q, 0, nq, cx, ctr, it_, in_, if_, my_umax, my_fmin);
     // one maximum per wave; the bounds only move one way, so a value read
     // earlier filters correctly
     if (SCOPE == __HIP_MEMORY_SCOPE_WORKGROUP) {
@@ -494,7 +521,7 @@ __device__ __forceinline__ void relax_arcs(const RGraph& g, const LayoutArc* lar
 
 // Expand the vertices cur[base .. base+nv) (nv <= WG) of a near list that
 // several workgroups share (team and plain forms).
-template <typename K, int WG, int SCOPE, typename C>
+template <typename K, int WG, int SCOPE, bool PRUNE, typename C>
 __device__ __forceinline__ void relax_block(const RGraph& g, K* key, uint32_t* flags, const int32_t* cur,
                                             int32_t base, int32_t nv, uint32_t curbit, const RelaxCtx& cx, C* ctr,
                                             int it_, int in_, int if_, unsigned long long* umax, Expand<K, WG>& X,
@@ -509,12 +536,12 @@ __device__ __forceinline__ void relax_block(const RGraph& g, K* key, uint32_t* f
         X.beg[tid] = b;
         X.key[tid] = ld<SCOPE>(&key[v]);
     }
-    expand_scan<K, WG>(X, deg);
+    expand_scan(X, deg);
     __syncthreads();
     uint32_t total;
-    const uint32_t wpre = expand_waves<K, WG>(X, total);
+    const uint32_t wpre = expand_waves<WG>(X, total);
     arcs += total;
-    relax_arcs<K, WG, SCOPE, false, C>(g, nullptr, key, flags, X, nv, wpre, total, cx, ctr, it_, in_, if_, umax, nullptr, Q);
+    relax_arcs<K, WG, SCOPE, PRUNE, false, C>(g, nullptr, key, flags, X, nv, wpre, total, cx, ctr, it_, in_, if_, umax, nullptr, Q);
     __syncthreads();
 }
 
@@ -706,8 +733,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
         if (prune) {
             for (int64_t i = p.poff[hg] + tid; i < p.poff[hg + 1]; i += WG) {
                 const uint64_t lx = p.plab[i];
-                const uint32_t x = p.dmaj ? (uint32_t)lx : (uint32_t)(lx >> 32), y = x ^ px;
-                const uint32_t dd = p.dmaj ? (uint32_t)(lx >> 32) : (uint32_t)lx;
+                const uint32_t x = (uint32_t)lx, y = x ^ px;
+                const uint32_t dd = (uint32_t)(lx >> 32);
                 if (x < (uint32_t)p.pbound && y < (uint32_t)p.pbound) {
                     if (HS) {
                         uint32_t s = hash_slot(y);
@@ -734,13 +761,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
         cx.lds = near_lds<WG>();
         cx.poff = p.poff;
         cx.plab = p.plab;
-        cx.pmin = p.pmin;
+        cx.head = p.head;
         cx.prune = prune;
         cx.dh = dh;
         cx.hk = HS ? H.k : nullptr;
         cx.pbound = (uint32_t)p.pbound;
         cx.dhmin = S.dhmin;
-        cx.dmaj = p.dmaj != 0;
         cx.rank_query = HYB;
         for (;;) {
             // ---- rounds inside the bucket until no near vertex is left
@@ -789,7 +815,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         mn = (ull)(kv >> 1);
                         cl = (uint32_t)(kv & 1);
                     }
-                    expand_scan<K, WG>(S.X, deg);
+                    expand_scan(S.X, deg);
                     if (test && ncur <= WG) {
                         const bool anycl = __ballot(cl != 0) != 0;
 #pragma unroll
@@ -801,7 +827,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                     }
                     __syncthreads();
                     uint32_t total;
-                    const uint32_t wpre = expand_waves<K, WG>(S.X, total);
+                    const uint32_t wpre = expand_waves<WG>(S.X, total);
                     if (test && ncur <= WG) {
                         mn = (ull)T;
                         cl = 0;
@@ -814,7 +840,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         if (cl == 0 && mn > um) { stopped = true; break; }
                     }
                     arcs += total;
-                    relax_arcs<K, WG, SC, LAY, int32_t>(p.g, p.larc, key, flags, S.X, nv, wpre, total, cx, S.ctr,
+                    relax_arcs<K, WG, SC, PRUNE, LAY, int32_t>(p.g, p.larc, key, flags, S.X, nv, wpre, total, cx, S.ctr,
                                                         B_TOUCHED, B_NEXT + (it + 1) % 3, B_FAR, &S.umax,
                                                         &S.fmin, &Q[w]);
                     if (base + WG < ncur) __syncthreads();      // X is used again
@@ -982,7 +1008,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
             for (int x = tid; x < HCAP; x += WG) H.k[x] = -1;
         if (prune && !HS)
             for (int64_t i = p.poff[hg] + tid; i < p.poff[hg + 1]; i += WG) {
-                const uint32_t x = p.dmaj ? (uint32_t)p.plab[i] : (uint32_t)(p.plab[i] >> 32), y = x ^ px;
+                const uint32_t x = (uint32_t)p.plab[i], y = x ^ px;
                 if (x < (uint32_t)p.pbound && y < (uint32_t)p.pbound) dh[y] = 0xFFFFFFFFu;
             }
         __syncthreads();
@@ -1053,7 +1079,7 @@ __global__ __launch_bounds__(WG) void k_tree_plain(TreeParams p, int32_t h, long
             cx.next = lists + (int64_t)((it + 1) & 1) * p.s.stride;
             cx.far = far;
             for (int32_t base = blockIdx.x * WG; base < ncur; base += gridDim.x * WG)
-                relax_block<K, WG, SC>(p.g, key, flags, cur, base, min(WG, ncur - base), curbit, cx,
+                relax_block<K, WG, SC, false>(p.g, key, flags, cur, base, min(WG, ncur - base), curbit, cx,
                                               (unsigned long long*)gs, G_TOUCHED, G_CNT0 + (it + 1) % 3, G_FAR,
                                               (unsigned long long*)&gs[G_UMAX], S.X, &Q[tid >> 6], arcs);
             if (gtid == 0) { gs[G_CNT0 + (it + 2) % 3] = 0; gs[G_SETTLED] += ncur; }
@@ -1306,8 +1332,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const int32_t hg = h ^ (int32_t)px;      // whose prefix labels give d(h, x)
             for (int64_t i = p.poff[hg] + tid; i < p.poff[hg + 1]; i += WG) {
                 const uint64_t lx = p.plab[i];
-                const uint32_t x = p.dmaj ? (uint32_t)lx : (uint32_t)(lx >> 32), y = x ^ px;
-                const uint32_t dd = p.dmaj ? (uint32_t)(lx >> 32) : (uint32_t)lx;
+                const uint32_t x = (uint32_t)lx, y = x ^ px;
+                const uint32_t dd = (uint32_t)(lx >> 32);
                 if (x < (uint32_t)p.pbound && y < (uint32_t)p.pbound) {
                     dh[y] = dd;
                     atomicMin(&S.dhmin, dd);
@@ -1369,13 +1395,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 cx.prune = prune;
                 cx.poff = p.poff;
                 cx.plab = p.plab;
-                cx.pmin = p.pmin;
+                cx.head = p.head;
                 cx.dh = dh;
                 cx.pbound = (uint32_t)p.pbound;
                 cx.dhmin = S.dhmin;
-                cx.dmaj = p.dmaj != 0;
                 for (int32_t base = trank * chunk; base < ncur; base += W * chunk)
-                    relax_block<K, WG, SC>(p.g, key, flags, cur, base, min(chunk, ncur - base), curbit, cx,
+                    relax_block<K, WG, SC, PRUNE>(p.g, key, flags, cur, base, min(chunk, ncur - base), curbit, cx,
                                                   (ull*)tw, T_TOUCHED, T_CNT0 + (it + 1) % 3, T_FAR,
                                                   (ull*)&tw[T_UMAX], S.X, &Q[tid >> 6], arcs);
                 if (leader) {
@@ -1618,7 +1643,7 @@ __device__ __forceinline__ void srelax(const TreeParams& p, SmallLds<K>& S, cons
             int su = valid ? slookup(S, u) : -1;
             const K seen = su >= 0 ? __hip_atomic_load(&S.keys[su], __ATOMIC_RELAXED, SCW) : KeyTraits<K>::INF;
             bool cand = valid && nk < seen;
-            if (PRUNE && cand && (!p.pmin || (uint64_t)S.dhmin + p.pmin[u] <= nd)) {
+            if (PRUNE && cand && (uint64_t)S.dhmin + (uint32_t)(p.head[(int64_t)u * PRUNE_HEAD] >> 32) <= nd) {
                 // rank-prefix pruning (Section 4.3), as in the other forms,
                 // with the root's prefix distances from the LDS table (and
                 // the same bound)
@@ -1626,7 +1651,7 @@ __device__ __forceinline__ void srelax(const TreeParams& p, SmallLds<K>& S, cons
                 for (int64_t i = lb; i < le && cand; i += 4) {
                     uint64_t lx[4];
 #pragma unroll
-                    for (int z = 0; z < 4; z++) lx[z] = i + z < le ? p.plab[i + z] : ~0ull;
+                    for (int z = 0; z < 4; z++) lx[z] = i + z < le ? p.plab_hub[i + z] : ~0ull;
 #pragma unroll
                     for (int z = 0; z < 4; z++) {
                         const uint32_t x = (uint32_t)(lx[z] >> 32);
@@ -1718,7 +1743,7 @@ __global__ __launch_bounds__(64) void k_tree_small(TreeParams p, int32_t* ovf, i
                 if (lane == 0) S.bad = 1;       // (the table stays at most half full)
             } else {
                 for (int64_t i = lb + lane; i < le; i += 64) {
-                    const uint64_t lx = p.plab[i];
+                    const uint64_t lx = p.plab_hub[i];
                     const uint32_t x = (uint32_t)(lx >> 32), y = x ^ px;
                     if (x < (uint32_t)p.pbound && y < (uint32_t)p.pbound) {
                         uint32_t s = shash(y, SPH);
@@ -1941,10 +1966,11 @@ static_assert(T_BAR < GW_ROOT && T_ABORT < GW_ROOT && T_BAR > GW_FILLP, "group w
 template <typename K, int WG>
 struct GroupLds {
     int64_t beg[WG];          // row start of the chunk's vertices
+    uint64_t trees[WG];       // trees to expand at each of them, a nibble each
     int32_t vtx[WG];          // the vertices
-    uint32_t msk[WG];         // trees to expand at each of them
-    uint32_t off[WG];         // exclusive scan of deg * popcount(msk)
-    uint32_t wsum[WG / 64];
+    uint32_t off[WG];         // exclusive scan of deg * trees within each wave's vertices
+    uint32_t wtot[WG / 64];   // work items of each wave's vertices
+    uint8_t ntree[WG];
     unsigned long long red64[WG / 64];
     int32_t hroot[GT];
     unsigned long long lmin[GT], lumax[GT];
@@ -1956,6 +1982,15 @@ struct GroupLds {
 
 // work items in flight per thread
 constexpr int GROUP_ILP = 4;
+
+// A wave's candidates, as WaveQueue, with the tree of each (bit 4 of m: prefix
+// labels beyond the head may prune it).
+template <typename K>
+struct GroupQueue {
+    K nk[64 * (GROUP_ILP + 1)];
+    int32_t u[64 * (GROUP_ILP + 1)];
+    uint8_t m[64 * (GROUP_ILP + 1)];
+};
 
 // What the relaxation of a group's work items needs besides the launch
 // parameters.
@@ -1975,100 +2010,152 @@ struct GroupCtx {
     int it;
 };
 
-// Relax the work items [e_lo, e_hi) of a round, GROUP_ILP per thread at a
-// time; decode(e, arc, tree, key of the expanded vertex) gives item e.
-// Improved (vertex, tree) pairs go to the next near list or the far list,
-// vertices reached for the first time by any tree to the touched list; the
-// per-tree largest clean distance, clean far pushes and counts accumulate
-// in LDS.
-template <typename K, int WG, bool PRUNE, typename D>
-__device__ __forceinline__ void group_relax(const TreeParams& p, const GroupCtx<K>& cx, GroupLds<K, WG>& S,
-                                            const uint32_t* dh, uint32_t e_lo, uint32_t e_hi, D decode) {
+// Test and apply nc candidates of a wave's queue, one per lane: improved
+// (vertex, tree) pairs go to the next near list or the far list, vertices
+// reached for the first time by any tree to the touched list; the per-tree
+// largest clean distance, clean far pushes and counts accumulate in LDS.
+template <typename K, int WG, bool PRUNE>
+__device__ __forceinline__ void group_settle(const TreeParams& p, const GroupCtx<K>& cx, GroupLds<K, WG>& S,
+                                             const uint32_t* dh, const GroupQueue<K>& Q, int first, int nc) {
     constexpr int SC = __HIP_MEMORY_SCOPE_AGENT;
     typedef unsigned long long ull;
-    for (uint32_t e0 = e_lo + threadIdx.x; e0 < e_hi; e0 += WG * GROUP_ILP) {
-        int tb[GROUP_ILP];
-        uint64_t a[GROUP_ILP];
-        K kv[GROUP_ILP], seen[GROUP_ILP];
-#pragma unroll
-        for (int j = 0; j < GROUP_ILP; j++) {
-            const uint32_t e = e0 + j * WG;
-            a[j] = 0; tb[j] = 0; kv[j] = 0;
-            if (e < e_hi) decode(e, a[j], tb[j], kv[j]);
-        }
-        // (lanes of one arc read the key line of its target once)
-#pragma unroll
-        for (int j = 0; j < GROUP_ILP; j++) {
-            const uint32_t e = e0 + j * WG;
-            seen[j] = e < e_hi ? ld<SC>(&cx.key[(int64_t)(a[j] >> 32) * GT + tb[j]]) : (K)0;
-        }
-#pragma unroll
-        for (int j = 0; j < GROUP_ILP; j++) {
-            const uint32_t e = e0 + j * WG;
-            const bool valid = e < e_hi;
-            const int b = tb[j];
-            const int32_t u = (int32_t)(a[j] >> 32);
-            const int32_t h = S.hroot[b];
-            const uint64_t nd = (uint64_t)(kv[j] >> 1) + (uint32_t)a[j];
-            const K nk = pack<K>(nd, (uint32_t)(kv[j] & 1) & (uint32_t)(u > h));
-            bool cand = valid && nk < seen[j];
-            if (PRUNE && cand && cx.pb && (!p.pmin || (uint64_t)S.dhmin[b] + p.pmin[u] <= nd)) {
-                // rank-prefix pruning (Section 4.3), as in the other forms,
-                // with this tree's root distances (and the same bound)
-                const uint32_t* dhb = dh + (int64_t)b * cx.pb;
-                const int64_t lb = p.poff[u], le = p.poff[u + 1];
-                for (int64_t i = lb; i < le && cand; i += 4) {
-                    uint64_t lx[4];
-#pragma unroll
-                    for (int z = 0; z < 4; z++) lx[z] = i + z < le ? p.plab[i + z] : ~0ull;
-#pragma unroll
-                    for (int z = 0; z < 4; z++) {
-                        const uint32_t x = p.dmaj ? (uint32_t)lx[z] : (uint32_t)(lx[z] >> 32);
-                        const uint32_t dd = p.dmaj ? (uint32_t)(lx[z] >> 32) : (uint32_t)lx[z];
-                        if (x >= cx.pb) continue;
-                        const uint32_t ax = dhb[x];
-                        if (ax != 0xFFFFFFFFu && (uint64_t)ax + dd <= nd) cand = false;
-                    }
-                    // groups ordered by distance: no later entry is closer
-                    if (p.dmaj && (uint64_t)(uint32_t)(lx[3] >> 32) + S.dhmin[b] > nd) break;
-                }
-            }
-            K old = seen[j];
-            if (cand) old = amin<SC>(&cx.key[(int64_t)u * GT + b], nk);
-            const bool imp = cand && nk < old;
-            const bool tonear = imp && (int64_t)nd < cx.T;
-            bool pnear = false, pfar = false, ptouch = false;
-            if (imp) {
-                if (nk & 1) {
-                    atomicMax(&S.lumax[b], (ull)nd);
-                    if (!tonear) atomicAdd(&S.lfcl[b], 1u);
-                }
-                if (tonear) {
-                    const uint32_t bit = 1u << (cx.nsh + (uint32_t)b);
-                    const uint32_t o = __hip_atomic_fetch_or(&cx.mask[u], bit, __ATOMIC_RELAXED, SC);
-                    pnear = ((o >> cx.nsh) & GBITS) == 0;
-                } else {
-                    const uint32_t o = aor<SC>(&cx.fmask[u], (1u << b) | GF_FAR_IN);
-                    pfar = (o & GF_FAR_IN) == 0;
-                }
-                if (old == KeyTraits<K>::INF) {
-                    const uint32_t o = aor<SC>(&cx.fmask[u], GF_TOUCHED);
-                    ptouch = (o & GF_TOUCHED) == 0;
-                }
-            }
-            int64_t q = wave_append(ptouch, (ull*)&cx.tw[GW_TOUCHEDL]);
-            if (ptouch && q < cx.n) lput<SC>(&cx.touched[q], u);
-            q = wave_append(pnear, (ull*)&cx.tw[GW_CNT0 + (cx.it + 1) % 3]);
-            if (pnear && q < cx.n) lput<SC>(&cx.next[q], u);
-            q = wave_append(pfar, (ull*)&cx.tw[GW_FARL]);
-            if (pfar && q < cx.n) lput<SC>(&cx.far[q], u);
-        }
+    const int lane = threadIdx.x & 63;
+    bool cand = lane < nc;
+    int32_t u = 0;
+    uint32_t m = 0;
+    K nk = 0;
+    if (cand) { u = Q.u[first + lane]; nk = Q.nk[first + lane]; m = Q.m[first + lane]; }
+    const int b = (int)(m & (GT - 1));
+    const uint64_t nd = (uint64_t)(nk >> 1);
+    K* kp = &cx.key[(int64_t)u * GT + b];
+    // (lanes of one arc read the key line of its target once)
+    if (cand) cand = nk < ld<SC>(kp);
+    if (PRUNE && cand && (m >> 4)) {
+        const uint32_t* dhb = dh + (int64_t)b * cx.pb;
+        cand = !tail_test(p.poff, p.plab, u, nd, cx.pb, S.dhmin[b], [&](uint32_t x) { return dhb[x]; });
+    }
+    K old = 0;
+    if (cand) old = amin<SC>(kp, nk);
+    const bool imp = cand && nk < old, near = imp && (int64_t)nd < cx.T;
+    if (imp && (nk & 1)) {
+        atomicMax(&S.lumax[b], (ull)nd);
+        if (!near) atomicAdd(&S.lfcl[b], 1u);
+    }
+    uint32_t om = 0, of = 0;
+    if (near) om = __hip_atomic_fetch_or(&cx.mask[u], 1u << (cx.nsh + (uint32_t)b), __ATOMIC_RELAXED, SC);
+    // the far list's bits and, on a first visit, the touched bit
+    const bool first_visit = imp && old == KeyTraits<K>::INF, tofar = imp && !near;
+    if (tofar || first_visit)
+        of = aor<SC>(&cx.fmask[u], (tofar ? (1u << b) | GF_FAR_IN : 0u) | (first_visit ? GF_TOUCHED : 0u));
+    Append3<1, ull> ap;
+    ap.m[0][0] = __ballot(first_visit && (of & GF_TOUCHED) == 0);
+    ap.m[1][0] = __ballot(near && ((om >> cx.nsh) & GBITS) == 0);
+    ap.m[2][0] = __ballot(tofar && (of & GF_FAR_IN) == 0);
+    if (!ap.reserve((ull*)cx.tw, GW_TOUCHEDL, GW_CNT0 + (cx.it + 1) % 3, GW_FARL)) return;
+    if (ap.m[0][0] >> lane & 1) {
+        const int64_t q = ap.at(0, 0);
+        if (q < cx.n) lput<SC>(&cx.touched[q], u);
+    }
+    if (ap.m[1][0] >> lane & 1) {
+        const int64_t q = ap.at(1, 0);
+        if (q < cx.n) lput<SC>(&cx.next[q], u);
+    }
+    if (ap.m[2][0] >> lane & 1) {
+        const int64_t q = ap.at(2, 0);
+        if (q < cx.n) lput<SC>(&cx.far[q], u);
     }
 }
 
-__device__ __forceinline__ int nth_bit(uint32_t m, int j) {
-    for (int k = 0; k < j; k++) m &= m - 1;
-    return __ffs(m) - 1;
+// Relax the arcs of the chunk in S (nv vertices, total work items, wpre as
+// expand_waves gives it). The items (vertex, arc, tree) run with the trees
+// fastest, so that the lanes of one arc read the arc and its target's head
+// and keys once.
+template <typename K, int WG, bool PRUNE>
+__device__ __forceinline__ void group_relax(const TreeParams& p, const GroupCtx<K>& cx, GroupLds<K, WG>& S,
+                                            const uint32_t* dh, GroupQueue<K>& Q, int32_t nv, uint32_t wpre,
+                                            uint32_t total) {
+    constexpr int SC = __HIP_MEMORY_SCOPE_AGENT;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int nw = (nv + 63) >> 6;
+    const int wtop = nw > 1 ? 1 << (31 - __clz(nw - 1)) : 0;
+    const int n1 = min(nv, 64);
+    const int ltop = n1 > 1 ? 1 << (31 - __clz(n1 - 1)) : 0;
+    int nq = 0;
+#pragma unroll 1
+    for (uint32_t eb = (uint32_t)(tid & ~63); eb < total; eb += WG * GROUP_ILP) {
+        int32_t u[GROUP_ILP];
+        int tb[GROUP_ILP];
+        K nk[GROUP_ILP];
+        bool cand[GROUP_ILP];
+        {
+            int own[GROUP_ILP];
+            uint32_t rel[GROUP_ILP];
+            uint64_t a[GROUP_ILP];
+#pragma unroll
+            for (int j = 0; j < GROUP_ILP; j++) own[j] = 0;
+#pragma unroll 1
+            for (int s = wtop; s > 0; s >>= 1)
+#pragma unroll
+                for (int j = 0; j < GROUP_ILP; j++) {
+                    const int t = own[j] + s;
+                    if (__shfl(wpre, t) <= eb + j * WG + lane) own[j] = t;
+                }
+#pragma unroll
+            for (int j = 0; j < GROUP_ILP; j++) {
+                rel[j] = eb + j * WG + lane - __shfl(wpre, own[j]);
+                own[j] = (own[j] * 64) & (WG - 1);    // (beyond the last item: any vertex)
+            }
+#pragma unroll 1
+            for (int s = ltop; s > 0; s >>= 1)
+#pragma unroll
+                for (int j = 0; j < GROUP_ILP; j++)
+                    if (S.off[own[j] + s] <= rel[j]) own[j] += s;
+#pragma unroll
+            for (int j = 0; j < GROUP_ILP; j++) {
+                const bool in = eb + j * WG + lane < total;
+                const uint32_t r = rel[j] - S.off[own[j]];
+                const uint32_t nt = max(1u, (uint32_t)S.ntree[own[j]]), q = r / nt;
+                tb[j] = (int)(S.trees[own[j]] >> (4 * (r - q * nt))) & (GT - 1);
+                a[j] = in ? p.g.arc[S.beg[own[j]] + q] : 0;
+                nk[j] = in ? ld<SC>(&cx.key[(int64_t)S.vtx[own[j]] * GT + tb[j]]) : (K)0;
+            }
+#pragma unroll
+            for (int j = 0; j < GROUP_ILP; j++) {
+                u[j] = (int32_t)(a[j] >> 32);
+                nk[j] = pack<K>((uint64_t)(nk[j] >> 1) + (uint32_t)a[j],
+                                (uint32_t)(nk[j] & 1) & (uint32_t)(u[j] > S.hroot[tb[j]]));
+            }
+        }
+        if constexpr (PRUNE) {
+            uint64_t e4[GROUP_ILP][PRUNE_HEAD];
+#pragma unroll
+            for (int j = 0; j < GROUP_ILP; j++) load_head(p.head, u[j], e4[j]);   // (vertex 0 beyond the last item)
+#pragma unroll
+            for (int j = 0; j < GROUP_ILP; j++) {
+                bool pruned = false, more = false;
+                const uint32_t* dhb = dh + (int64_t)tb[j] * cx.pb;
+                head_test(e4[j], (uint64_t)(nk[j] >> 1), cx.pb, S.dhmin[tb[j]], [&](uint32_t x) { return dhb[x]; },
+                          pruned, more);
+                cand[j] = eb + j * WG + lane < total && !pruned;
+                if (more) tb[j] |= GT;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < GROUP_ILP; j++) cand[j] = eb + j * WG + lane < total;
+        }
+#pragma unroll
+        for (int j = 0; j < GROUP_ILP; j++) {
+            const uint64_t m = __ballot(cand[j]);
+            const int q = nq + (int)lanes_below(m);
+            if (cand[j]) { Q.nk[q] = nk[j]; Q.u[q] = u[j]; Q.m[q] = (uint8_t)tb[j]; }
+            nq += (int)__popcll(m);
+        }
+        wave_sync();
+#pragma unroll 1
+        for (; nq >= 64; nq -= 64) group_settle<K, WG, PRUNE>(p, cx, S, dh, Q, nq - 64, 64);
+        wave_sync();
+    }
+    if (nq > 0) group_settle<K, WG, PRUNE>(p, cx, S, dh, Q, 0, nq);
 }
 
 template <typename K, int WG, bool PRUNE>
@@ -2077,6 +2164,7 @@ __global__ __launch_bounds__(WG) void k_tree_group(TreeParams p, int W, long lon
     constexpr int SC = __HIP_MEMORY_SCOPE_AGENT;
     typedef unsigned long long ull;
     __shared__ GroupLds<K, WG> S;
+    __shared__ GroupQueue<K> Q[WG / 64];
     extern __shared__ uint32_t dh[];     // [GT][pbound]: each tree's root distances to the prefix hubs
     const int tid = threadIdx.x;
     const int lb = team_index(blockIdx.x, gridDim.x, p.xcd_map);
@@ -2149,8 +2237,8 @@ __global__ __launch_bounds__(WG) void k_tree_group(TreeParams p, int W, long lon
                 const int32_t hg = h ^ (int32_t)px;
                 for (int64_t i = p.poff[hg] + tid; i < p.poff[hg + 1]; i += WG) {
                     const uint64_t lx = p.plab[i];
-                    const uint32_t x = p.dmaj ? (uint32_t)lx : (uint32_t)(lx >> 32), y = x ^ px;
-                    const uint32_t dd = p.dmaj ? (uint32_t)(lx >> 32) : (uint32_t)lx;
+                    const uint32_t x = (uint32_t)lx, y = x ^ px;
+                    const uint32_t dd = (uint32_t)(lx >> 32);
                     if (x < pb && y < pb) {
                         dh[b * pb + y] = dd;
                         atomicMin(&S.dhmin[b], dd);
@@ -2215,9 +2303,7 @@ __global__ __launch_bounds__(WG) void k_tree_group(TreeParams p, int W, long lon
                     if (!alive) break;
                 }
                 // ---- relax: the near list split evenly over the team's
-                //      workgroups; each chunk's work items are (vertex, arc,
-                //      tree) triples, trees fastest, so that consecutive lanes
-                //      read the same arc and the same key line
+                //      workgroups
                 const GroupCtx<K> cx{key, mask, fmask, touched, next, far, tw, T, nsh, pb, n, it};
                 const int32_t chunk = min(WG, (ncur + W - 1) / W);
                 if (tid < GT) { S.lumax[tid] = 0; S.lfcl[tid] = 0; S.lset[tid] = 0; S.larc[tid] = 0; }
@@ -2237,28 +2323,20 @@ __global__ __launch_bounds__(WG) void k_tree_group(TreeParams p, int W, long lon
                             atomicAdd(&S.lset[b], 1ull);
                             atomicAdd(&S.larc[b], (ull)deg);
                         }
+                        uint64_t trees = 0;
+                        int nt = 0;
+                        for (uint32_t mm = m; mm; mm &= mm - 1) trees |= (uint64_t)(__ffs(mm) - 1) << (4 * nt++);
                         S.beg[tid] = b0;
                         S.vtx[tid] = v;
-                        S.msk[tid] = m;
-                        items = deg * (uint32_t)__popc(m);
+                        S.trees[tid] = trees;
+                        S.ntree[tid] = (uint8_t)nt;
+                        items = deg * (uint32_t)nt;
                     }
-                    uint32_t total;
-                    const uint32_t ex = block_scan<WG>(items, S.wsum, total);   // (synchronises the block)
-                    S.off[tid] = ex;
+                    expand_scan(S, items);
                     __syncthreads();
-                    group_relax<K, WG, PRUNE>(p, cx, S, dh, 0, total, [&](uint32_t e, uint64_t& a, int& b, K& kv) {
-                        int lo = 0, hi = nv - 1;
-                        while (lo < hi) {
-                            const int mid = (lo + hi + 1) >> 1;
-                            if (S.off[mid] <= e) lo = mid; else hi = mid - 1;
-                        }
-                        const uint32_t m = S.msk[lo];
-                        const uint32_t pc = (uint32_t)max(1, __popc(m));
-                        const uint32_t r = e - S.off[lo];
-                        b = nth_bit(m, (int)(r % pc));
-                        a = p.g.arc[S.beg[lo] + r / pc];
-                        kv = ld<SC>(&key[(int64_t)S.vtx[lo] * GT + b]);
-                    });
+                    uint32_t total;
+                    const uint32_t wpre = expand_waves<WG>(S, total);
+                    group_relax<K, WG, PRUNE>(p, cx, S, dh, Q[tid >> 6], nv, wpre, total);
                     __syncthreads();
                 }
                 if (tid < GT) {

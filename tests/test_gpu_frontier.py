@@ -79,3 +79,20 @@ def test_input_numbering(rows, cols, directed):
             assert np.array_equal(hub, refs[0].hub_pos[want])
             assert np.array_equal(dist.astype(np.int64), refs[0].dist[want])
             L.free()
+
+
+@pytest.mark.parametrize("hubs", [1, 2, 3, 4, 5, 6, 12, 13, 100])
+@pytest.mark.parametrize("wmax", [2, 1 << 22])
+def test_prefix_label_counts(hubs, wmax):
+    """Pruning with prefixes whose per-vertex label lists end before, at and
+    just behind the labels tested first and the batches read after them, with
+    32- and 64-bit keys, in the batched, team, group and small-tree kernels."""
+    print("prefix labels", hubs, wmax, flush=True)
+    n, u, v, w = gg.random_edges(700, 1500, 1, wmax, hubs)
+    row, col, ww = gg.to_csr(n, u, v, w)
+    order = gg.random_rank(n, hubs)
+    ref = oracle.chl(row, col, ww, order)
+    for kw in (dict(team_wgs=1, wg_size=64), dict(team_wgs=3), dict(), dict(groups=False, small=True)):
+        L, off, hub, dist = gpu_labels(row, col, ww, order, autotune=False, prune_hubs=hubs, delta=1 + wmax // 2, **kw)
+        assert_same_labels(off, hub, dist, ref, str((hubs, wmax, kw)))
+        L.free()
