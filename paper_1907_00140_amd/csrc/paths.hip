@@ -11,12 +11,14 @@
 // L_p are looked up in L_v. slot = the position of p's label of the same hub
 // within L_p, so that a walk takes one step per edge.
 //
-// k_parents: one wave per vertex v, vertices taken from a queue in rank
-// order (an atomic counter over hub_vertex[]: under a degree ranking the
-// heaviest rows go first, and no wave is left with a run of them, as a fixed
-// stride over input ids would leave one on an R-MAT graph, whose
-// high-degree ids are those with few bits set). A pass whose labels are all
-// v's own (distance 0, no parent) skips the arcs. L_v (up to PCH labels per
+// k_parents: one wave per vertex v, each wave taking every 32768th (or fewer)
+// rank position, so that under a degree ranking no wave is left with a run
+// of heavy rows, as a fixed stride over input ids would leave one on an
+// R-MAT graph (whose high-degree ids are those with few bits set); a queue
+// over the rank order spent longer on its one counter (65,536 vertices:
+// 1.1 ms) than on the lookups. Vertices with many arcs take 16 waves each
+// (k_parents_heavy). A pass whose labels are all v's own (distance 0, no
+// parent) skips the arcs. L_v (up to PCH labels per
 // pass) sits in LDS as sorted hubs, distances and a 64-bit candidate
 // (p << 32 | slot) per label. The arcs of v are taken 64 at a time; each lane owns one arc and
 // the wave splits the flattened (arc, entry of L_p) index space evenly over
@@ -48,11 +50,25 @@ namespace {
 
 constexpr int PW = 4;       // waves per workgroup of k_parents
 constexpr int PCH = 256;    // labels of L_v per LDS pass
+constexpr int HW = 16;      // waves that share a heavy vertex
+// A vertex of more arcs than this is heavy: 16 waves take its arcs, 64 at a
+// time, against the same labels in LDS. One wave per vertex left a build's
+// most important vertices (thousands of arcs each) running long after the
+// rest. Parents of R-MAT 16 / R-MAT 20, with the queue that handed single
+// vertices to waves: 1.65 / 20.3 ms; without it and with the line at 512 arcs
+// 0.49 / 9.9, at 256 0.41 / 9.9, at 128 0.54 / 17.4 (eight waves, 128 arcs:
+// 0.39 / 12.6).
+constexpr int64_t HEAVY_ARCS = 256;
 
-struct ParentLds {
+// labels of the vertex (shared by the waves that work on it)
+struct LabelLds {
     unsigned long long cand[PCH];
     int32_t hub[PCH];
     int32_t dist[PCH];
+};
+
+// 64 arcs of a wave
+struct ArcLds {
     int64_t inc[64];        // inclusive scan of the (cut) list lengths of the 64 arcs
     int64_t beg[64];        // first entry of each arc's (cut) list
     int64_t base[64];       // off[p] of each arc (slot = entry - base)
@@ -77,100 +93,140 @@ __device__ __forceinline__ int64_t lower_hub(const int32_t* __restrict__ hub, in
     return lo;
 }
 
-__global__ __launch_bounds__(64 * PW) void k_parents(int32_t n, int64_t m, const int64_t* __restrict__ row,
-                                                     const int32_t* __restrict__ col, const int32_t* __restrict__ wt,
-                                                     const int64_t* __restrict__ off, const int32_t* __restrict__ hub,
-                                                     const int32_t* __restrict__ dist, int32_t* __restrict__ parent,
-                                                     int32_t* __restrict__ slot, const int32_t* __restrict__ vorder,
-                                                     unsigned long long* next, int32_t* err) {
-    __shared__ ParentLds lds[PW];
-    const int lane = threadIdx.x & 63;
-    ParentLds& S = lds[threadIdx.x >> 6];
-    for (;;) {
-        unsigned long long idx = 0;
-        if (lane == 0) idx = atomicAdd(next, 1ull);
-        idx = __shfl(idx, 0);
-        if (idx >= (unsigned long long)n) break;
+struct ParentArgs {
+    int32_t n;
+    int64_t m;
+    const int64_t* row;
+    const int32_t* col;
+    const int32_t* wt;
+    const int64_t* off;
+    const int32_t* hub;
+    const int32_t* dist;
+    int32_t* parent;
+    int32_t* slot;
+    int32_t* err;
+};
+
+// Parents of v's labels by W waves (W = 1, or a whole workgroup).
+template <int W>
+__device__ __forceinline__ void parents_of(const ParentArgs& a, int32_t v, LabelLds& S, ArcLds& R) {
+    const int lane = threadIdx.x & 63, wave = W > 1 ? threadIdx.x >> 6 : 0;
+    const int gl = W > 1 ? threadIdx.x : lane;
+    auto sync = [&]() { if (W > 1) __syncthreads(); else wave_sync(); };
+    const int64_t lb = a.off[v], le = a.off[v + 1];
+    int64_t eb = a.row[v], ee = a.row[v + 1];
+    if (eb < 0 || ee < eb || ee > a.m) {          // malformed row: no arcs, flagged
+        if (gl == 0) atomicOr(a.err, ERR_BIT_INVALID);
+        eb = ee = 0;
+    }
+    for (int64_t c0 = lb; c0 < le; c0 += PCH) {
+        const int cn = (int)std::min<int64_t>(PCH, le - c0);
+        for (int i = gl; i < cn; i += 64 * W) {
+            S.hub[i] = a.hub[c0 + i];
+            S.dist[i] = a.dist[c0 + i];
+            S.cand[i] = ~0ull;
+        }
+        const bool whole = c0 == lb && c0 + cn == le;
+        const int32_t hlo = a.hub[c0], hhi = a.hub[c0 + cn - 1];
+        bool far = false;                          // some label of the pass is not v's own
+        for (int i = lane; i < cn; i += 64) far |= a.dist[c0 + i] != 0;
+        const bool any_far = __ballot(far) != 0;
+        sync();
+        for (int64_t e0 = any_far ? eb + 64 * wave : ee; e0 < ee; e0 += 64 * W) {
+            const int64_t e = e0 + lane;
+            int64_t len = 0, beg = 0, base = 0;
+            int32_t p = 0, w = 0;
+            if (e < ee) {
+                p = a.col[e];
+                w = a.wt[e];
+                if (p >= 0 && p < a.n && w >= 1) {
+                    base = a.off[p];
+                    int64_t end = a.off[p + 1];
+                    beg = !whole ? lower_hub(a.hub, base, end, hlo) : base;
+                    if (end > beg && a.hub[end - 1] > hhi) end = lower_hub(a.hub, beg, end, hhi + 1);
+                    len = end - beg;
+                } else {
+                    atomicOr(a.err, ERR_BIT_INVALID);
+                }
+            }
+            int64_t inc = len;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int64_t t = __shfl_up(inc, d);
+                if (lane >= d) inc += t;
+            }
+            R.inc[lane] = inc;
+            R.beg[lane] = beg;
+            R.base[lane] = base;
+            R.p[lane] = p;
+            R.w[lane] = w;
+            const int64_t total = __shfl(inc, 63);
+            wave_sync();
+            for (int64_t t = lane; t < total; t += 64) {
+                int x = 0, z = 63;                     // first arc with inc > t
+                while (x < z) {
+                    const int mid = (x + z) >> 1;
+                    if (R.inc[mid] > t) z = mid; else x = mid + 1;
+                }
+                const int64_t j = R.beg[x] + (t - (x ? R.inc[x - 1] : 0));
+                const int32_t hj = a.hub[j];
+                int lo = 0, hi = cn;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (S.hub[mid] < hj) lo = mid + 1; else hi = mid;
+                }
+                if (lo < cn && S.hub[lo] == hj && (int64_t)a.dist[j] + R.w[x] == (int64_t)S.dist[lo])
+                    atomicMin(&S.cand[lo], ((unsigned long long)(uint32_t)R.p[x] << 32) |
+                                               (uint32_t)(j - R.base[x]));
+            }
+            wave_sync();
+        }
+        sync();
+        for (int i = gl; i < cn; i += 64 * W) {
+            const unsigned long long c = S.cand[i];
+            a.parent[c0 + i] = c == ~0ull ? -1 : (int32_t)(c >> 32);
+            a.slot[c0 + i] = c == ~0ull ? -1 : (int32_t)(uint32_t)c;
+        }
+        sync();
+    }
+}
+
+__global__ __launch_bounds__(64 * PW) void k_parents(ParentArgs a, const int32_t* __restrict__ vorder) {
+    __shared__ LabelLds S[PW];
+    __shared__ ArcLds R[PW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int64_t idx = (int64_t)blockIdx.x * PW + w; idx < a.n; idx += (int64_t)gridDim.x * PW) {
         const int32_t v = vorder[idx];
-        if (v < 0 || v >= n) {
-            if (lane == 0) atomicOr(err, ERR_BIT_INVALID);
+        if (v < 0 || v >= a.n) {
+            if (lane == 0) atomicOr(a.err, ERR_BIT_INVALID);
             continue;
         }
-        const int64_t lb = off[v], le = off[v + 1];
-        int64_t eb = row[v], ee = row[v + 1];
-        if (eb < 0 || ee < eb || ee > m) {          // malformed row: no arcs, flagged
-            if (lane == 0) atomicOr(err, ERR_BIT_INVALID);
-            eb = ee = 0;
+        if (a.row[v + 1] - a.row[v] > HEAVY_ARCS) continue;      // k_parents_heavy
+        parents_of<1>(a, v, S[w], R[w]);
+    }
+}
+
+// The heavy vertices: a workgroup looks 1024 vertices over at a time, those of
+// neighbouring rank positions going to different workgroups (under a degree
+// ranking the heavy ones are neighbours in rank).
+__global__ __launch_bounds__(64 * HW) void k_parents_heavy(ParentArgs a, const int32_t* __restrict__ vorder) {
+    __shared__ LabelLds S;
+    __shared__ ArcLds R[HW];
+    __shared__ int32_t list[64 * HW];
+    __shared__ int32_t count;
+    const int w = threadIdx.x >> 6;
+    for (int64_t i0 = blockIdx.x; i0 < a.n; i0 += (int64_t)gridDim.x * 64 * HW) {
+        if (threadIdx.x == 0) count = 0;
+        __syncthreads();
+        const int64_t i = i0 + (int64_t)threadIdx.x * gridDim.x;
+        if (i < a.n) {
+            const int32_t v = vorder[i];
+            if (v >= 0 && v < a.n && a.row[v + 1] - a.row[v] > HEAVY_ARCS) list[atomicAdd(&count, 1)] = v;
         }
-        for (int64_t c0 = lb; c0 < le; c0 += PCH) {
-            const int cn = (int)std::min<int64_t>(PCH, le - c0);
-            for (int i = lane; i < cn; i += 64) {
-                S.hub[i] = hub[c0 + i];
-                S.dist[i] = dist[c0 + i];
-                S.cand[i] = ~0ull;
-            }
-            const bool whole = c0 == lb && c0 + cn == le;
-            const int32_t hlo = hub[c0], hhi = hub[c0 + cn - 1];
-            bool far = false;                          // some label of the pass is not v's own
-            for (int i = lane; i < cn; i += 64) far |= dist[c0 + i] != 0;
-            const bool any_far = __ballot(far) != 0;
-            wave_sync();
-            for (int64_t e0 = any_far ? eb : ee; e0 < ee; e0 += 64) {
-                const int64_t e = e0 + lane;
-                int64_t len = 0, beg = 0, base = 0;
-                int32_t p = 0, w = 0;
-                if (e < ee) {
-                    p = col[e];
-                    w = wt[e];
-                    if (p >= 0 && p < n && w >= 1) {
-                        base = off[p];
-                        int64_t end = off[p + 1];
-                        beg = !whole ? lower_hub(hub, base, end, hlo) : base;
-                        if (end > beg && hub[end - 1] > hhi) end = lower_hub(hub, beg, end, hhi + 1);
-                        len = end - beg;
-                    } else {
-                        atomicOr(err, ERR_BIT_INVALID);
-                    }
-                }
-                int64_t inc = len;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const int64_t t = __shfl_up(inc, d);
-                    if (lane >= d) inc += t;
-                }
-                S.inc[lane] = inc;
-                S.beg[lane] = beg;
-                S.base[lane] = base;
-                S.p[lane] = p;
-                S.w[lane] = w;
-                const int64_t total = __shfl(inc, 63);
-                wave_sync();
-                for (int64_t t = lane; t < total; t += 64) {
-                    int a = 0, z = 63;                     // first arc with inc > t
-                    while (a < z) {
-                        const int mid = (a + z) >> 1;
-                        if (S.inc[mid] > t) z = mid; else a = mid + 1;
-                    }
-                    const int64_t j = S.beg[a] + (t - (a ? S.inc[a - 1] : 0));
-                    const int32_t hj = hub[j];
-                    int lo = 0, hi = cn;
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (S.hub[mid] < hj) lo = mid + 1; else hi = mid;
-                    }
-                    if (lo < cn && S.hub[lo] == hj && (int64_t)dist[j] + S.w[a] == (int64_t)S.dist[lo])
-                        atomicMin(&S.cand[lo], ((unsigned long long)(uint32_t)S.p[a] << 32) |
-                                                   (uint32_t)(j - S.base[a]));
-                }
-                wave_sync();
-            }
-            for (int i = lane; i < cn; i += 64) {
-                const unsigned long long c = S.cand[i];
-                parent[c0 + i] = c == ~0ull ? -1 : (int32_t)(c >> 32);
-                slot[c0 + i] = c == ~0ull ? -1 : (int32_t)(uint32_t)c;
-            }
-            wave_sync();
-        }
+        __syncthreads();
+        const int32_t c = count;
+        for (int32_t k = 0; k < c; k++) parents_of<HW>(a, list[k], S, R[w]);
+        __syncthreads();
     }
 }
 
@@ -336,19 +392,18 @@ extern "C" int chl_labels_parents(const chl_labels* h, const chl_graph* g, int32
     if (h->total > 0 && (!parent || !slot)) return CHL_ERR_INVALID_ARG;
     if (h->total == 0 || h->n == 0) return CHL_OK;
     hipStream_t st = (hipStream_t)stream;
-    // the vertex queue's counter
-    auto* next = (unsigned long long*)h->alloc.alloc(256, h->alloc.ctx);
-    if (!next) return CHL_ERR_OOM;
-    const int rc = with_err(h, st, [&]() {
-        if (hipMemsetAsync(next, 0, 8, st) != hipSuccess) return CHL_ERR_HIP;
-        const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(((int64_t)h->n + PW - 1) / PW, 2048));
-        hipLaunchKernelGGL(k_parents, dim3(blocks), dim3(64 * PW), 0, st, h->n, g->n_arcs, g->row_ptr, g->col,
-                           g->w, h->offsets, h->hub_pos, h->dist, parent, slot, h->order, next, h->qerr);
+    return with_err(h, st, [&]() {
+        const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(((int64_t)h->n + PW - 1) / PW, 8192));
+        const ParentArgs a{h->n,       g->n_arcs, g->row_ptr, g->col, g->w,   h->offsets,
+                           h->hub_pos, h->dist,   parent,     slot,   h->qerr};
+        // (the heavy vertices first: the others fill the device beside the
+        // last of them)
+        const int64_t hblocks = std::max<int64_t>(1, std::min<int64_t>(h->n, 512));
+        if (g->n_arcs > HEAVY_ARCS)
+            hipLaunchKernelGGL(k_parents_heavy, dim3(hblocks), dim3(64 * HW), 0, st, a, h->order);
+        hipLaunchKernelGGL(k_parents, dim3(blocks), dim3(64 * PW), 0, st, a, h->order);
         return hipGetLastError() == hipSuccess ? CHL_OK : CHL_ERR_HIP;
     });
-    (void)hipStreamSynchronize(st);
-    h->alloc.free(next, h->alloc.ctx);
-    return rc;
 }
 
 extern "C" int chl_query_path_hops(const chl_labels* h, const int32_t* parent, const int32_t* slot,

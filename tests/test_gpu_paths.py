@@ -223,3 +223,23 @@ def test_paths_after_pruned_and_team_builds():
             ref = (par, slot, paths)
         else:
             _same((par, slot, paths), ref, str(kw))
+
+
+@pytest.mark.parametrize("leaves", [255, 256, 257, 1025, 3000])
+def test_parents_heavy_vertices(leaves):
+    """Vertices around and far beyond the arc count from which several waves
+    share a vertex, important and unimportant ones, with ties."""
+    print("heavy vertices", leaves, flush=True)
+    g = np.random.default_rng(leaves)
+    e = [(0, 3 + i, int(g.integers(1, 4))) for i in range(leaves)]
+    e += [(1, 3 + i, int(g.integers(1, 4))) for i in range(0, leaves, 2)]
+    e += [(2, 3 + i, int(g.integers(1, 4))) for i in range(0, leaves, 3)]
+    row, col, w = pins.csr_from_edges(leaves + 3, e)
+    for order in (gg.degree_rank(row, 1), gg.random_rank(leaves + 3, 2)):
+        from paper_1907_00140_amd import chl
+        L = chl.build(row, col, w, order, autotune=False)
+        ref = oracle.chl(row, col, w, order)
+        par, slot = L.parents(row, col, w)
+        rpar, rslot = oracle.parents(ref, row, col, w)
+        assert np.array_equal(par.cpu().numpy(), rpar) and np.array_equal(slot.cpu().numpy(), rslot)
+        L.free()
