@@ -156,6 +156,7 @@ struct TuneVal {
     int k, wg;          // trees in flight, workgroup size
     int64_t delta;      // bucket width
     bool small = false; // main phase by the small-tree kernel (LDS), the others as fallback
+    double labels = 0;  // estimate of the main phase's labels
 };
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneVal> g_tune;
@@ -261,6 +262,31 @@ int grow_pool(Arena& A, Build& B, unsigned long long used, unsigned long long wa
     A.drop(B.pool.dist);
     B.pool = np;
     return 0;
+}
+
+// Make room for about `more` labels behind the first `used`, if memory allows;
+// the pool stays as it is otherwise (it grows on demand).
+void reserve_pool(Arena& A, Build& B, unsigned long long used, double more, hipStream_t st) {
+    size_t freeb = 0, totalb = 0;
+    if (hipMemGetInfo(&freeb, &totalb) != hipSuccess) return;
+    const double want = (double)used + 1.05 * more + 4096;
+    if (want <= (double)B.pool.cap || 12 * want > (double)(freeb / 2)) return;
+    Pool np = B.pool;
+    np.cap = (unsigned long long)want;
+    np.v = A.get<int32_t>(np.cap);
+    np.hub = np.v ? A.get<int32_t>(np.cap) : nullptr;
+    np.dist = np.hub ? A.get<int32_t>(np.cap) : nullptr;
+    bool ok = np.dist != nullptr;
+    if (ok && used)
+        ok = hipMemcpyAsync(np.v, B.pool.v, used * 4, hipMemcpyDeviceToDevice, st) == hipSuccess &&
+             hipMemcpyAsync(np.hub, B.pool.hub, used * 4, hipMemcpyDeviceToDevice, st) == hipSuccess &&
+             hipMemcpyAsync(np.dist, B.pool.dist, used * 4, hipMemcpyDeviceToDevice, st) == hipSuccess;
+    if (ok) ok = hipStreamSynchronize(st) == hipSuccess;
+    Pool& drop = ok ? B.pool : np;
+    for (void* p : {(void*)drop.v, (void*)drop.hub, (void*)drop.dist})
+        if (p) A.drop(p);
+    if (ok) B.pool = np;
+    A.oom = false;
 }
 
 TreeParams params(Build& B, const Slots& s, int64_t delta, int early, const int32_t* roots,
@@ -692,7 +718,8 @@ void chl_labels_free(chl_labels* h) {
 
 // ====================================================================== build
 static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_opts& o,
-                       hipStream_t st, int& k, int& wg, int64_t& delta, bool& small, double& tune_ms);
+                       hipStream_t st, int& k, int& wg, int64_t& delta, bool& small, double& labels,
+                       double& tune_ms);
 
 // The rank-prefix levels of a batched build (see chl_build_impl): grows the
 // trees of the roots [0, grown) and leaves their labels in the pool, the
@@ -1296,7 +1323,8 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
             A.oom = false;      // no room for the copy: the trees grow by rank position
         }
     }
-    if (int r = pick_params(A, B, g, o, st, k, wg, delta, small, tune_ms)) return r;
+    double main_labels = 0;
+    if (int r = pick_params(A, B, g, o, st, k, wg, delta, small, main_labels, tune_ms)) return r;
     S.small_trees = small ? small_capacity(B.key_bits) : 0;
     S.tune_ms = tune_ms;
     S.roots_in_flight = k;
@@ -1310,6 +1338,11 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
             hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess)
             S.clock_khz = khz;
     }
+
+    // A complete build whose label count is known roughly takes its pool at
+    // once: growing it by doubling stops the launch each time, and the trees
+    // in flight are grown again (512x512 grid: four times, 180M labels).
+    if (main_labels > 0 && o.root_count == 0) reserve_pool(A, B, B.cursor_base, main_labels, st);
 
     // ---- trees
     Slots s{};
@@ -1437,7 +1470,7 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
 
 // ---------------------------------------------------------------- tuner
 static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_opts& o, hipStream_t st,
-                       int& k, int& wg, int64_t& delta, bool& small, double& tune_ms) {
+                       int& k, int& wg, int64_t& delta, bool& small, double& labels, double& tune_ms) {
     const int32_t n = B.n;
     const double wmean = 0.5 * (1.0 + B.maxw);
     size_t freeb = 0, totalb = 0;
@@ -1458,7 +1491,7 @@ static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_o
     if (!need) return 0;
     // (unpruned builds share one entry whether or not their first roots ran
     // as a level)
-    TuneKey key{n, B.m, B.maxw, (o.mode * 8192 + (B.pbound ? B.grown : 0)) * 8192 + B.pbound, B.sig};
+    TuneKey key{n, B.m, B.maxw, ((o.hybrid_psi > 0 ? 2 : o.mode) * 8192 + (B.pbound ? B.grown : 0)) * 8192 + B.pbound, B.sig};
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune.find(key);
@@ -1467,6 +1500,7 @@ static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_o
             if (!o.wg_size) wg = it->second.wg;
             if (!o.delta) delta = it->second.delta;
             if (!o.small_trees) small = it->second.small;
+            labels = it->second.labels;
             return 0;
         }
     }
@@ -1486,7 +1520,12 @@ static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_o
     make_probe(strata);
     if (probe.empty()) return 0;
     int64_t* saved_stats = B.stats;
-    B.stats = nullptr;              // probe runs leave no statistics
+    B.stats = nullptr;              // probe runs leave no statistics behind
+    // (those of the last sizing run, in an array of their own, tell how the
+    // trees look; without room for it the tuner goes by the times alone)
+    int64_t* own = A.get<int64_t>((size_t)n * STAT_COLS);
+    int64_t* sums = own ? A.get<int64_t>(4) : nullptr;
+    if (!sums) A.oom = false;
     auto t0 = std::chrono::steady_clock::now();
     double best = 1e30;
     TuneVal bv{k, wg, delta};
@@ -1519,46 +1558,77 @@ static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_o
         if (ms < best) { best = ms; bv = TuneVal{kk, w, d}; }
         return 0;
     };
-    // coordinate search: bucket width (coarse, then refined), workgroup
-    // size at a fixed thread count, then trees in flight
-    const int k0 = o.roots_in_flight ? k : std::min(kmax, 512);
-    const int w0 = o.wg_size ? wg : 512;
+    // trees in flight: as many workgroups as the device holds (the kernels
+    // take up to 128 registers per lane, 2^18 threads at once; more slots
+    // than that wait for others to end). The Hybrid's windows and supersteps
+    // hold multiples of that many roots, and larger ones have fewer regroupings
+    // and tails: four times as many there (R-MAT 15: 170 -> 145 ms).
+    const int threads = o.hybrid_psi > 0 ? 1 << 20 : 1 << 18;
+    auto fill = [&](int w) { return std::max(1, std::min(kmax, threads / w)); };
+    int w0 = o.wg_size ? wg : 256;
+    const int k0 = o.roots_in_flight ? k : fill(w0);
+    double avg_settled = 0, round_arcs = 0;
     {
         const int64_t d0 = o.delta ? delta : std::max<int64_t>(1, (int64_t)wmean);
         for (;;) {
             double ms = 0;
+            B.stats = sums ? own : nullptr;
             if (int r = time_once(std::max(1, std::min(k0, kmax)), w0, d0, ms)) return r;
+            B.stats = nullptr;
             if (ms >= 10.0 || strata >= std::min<int32_t>(rest, 1 << 18)) break;
             strata = std::min<int32_t>(std::min<int32_t>(rest, 1 << 18), 4 * strata);
             make_probe(strata);
         }
     }
+    if (sums) {
+        HostCtl* hc = host_ctl();
+        if (!hc) return CHL_ERR_HIP;
+        HIPCHK(hipMemcpyAsync(B.roots, probe.data(), probe.size() * 4, hipMemcpyHostToDevice, st));
+        HIPCHK(hipMemsetAsync(sums, 0, 32, st));
+        if (launch_root_sums((int32_t)probe.size(), B.roots, own, sums, st)) return CHL_ERR_HIP;
+        HIPCHK(hipMemcpyAsync(hc->sums, sums, 32, hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        avg_settled = (double)hc->sums[0] / strata;
+        round_arcs = (double)hc->sums[1] / (double)std::max<int64_t>(1, hc->sums[3]);
+        labels = (double)hc->sums[2] * rest / strata;
+    }
+    if (own) A.drop(own);
+    if (sums) A.drop(sums);
+    // Large unpruned trees: a probe's time is that of its largest tree, which
+    // says little about the throughput of many (it took 1024 threads and wide
+    // buckets for the 512x512 grid). The workgroup size follows the arcs of a
+    // round instead: a round of a few hundred leaves a larger workgroup waiting
+    // at its barriers, one of thousands is shared by it (512x512 grid, 430 arcs
+    // a round: 256 threads 177 ms, 512 208, 1024 290; R-MAT 15 under a random
+    // ranking, 10^4 arcs: 256 threads 176, 512 138, 1024 136). And of the
+    // bucket widths whose probe is within a fifth of the best, the narrowest,
+    // which relaxes the fewest arcs (grid: mean weight 177, four times that
+    // 204 ms), when every slot has many trees to grow.
+    const bool by_rounds = !B.pbound && round_arcs > 0 && avg_settled > 128;
+    if (by_rounds && !o.wg_size) w0 = round_arcs >= 2048 ? 512 : 256;
+    // coordinate search: bucket width (coarse, then refined), then workgroup
+    // size
+    const int kd = o.roots_in_flight ? k : fill(w0);
     if (!o.delta) {
         for (double f : {1.0 / 64, 1.0 / 16, 0.25, 1.0, 4.0})
-            if (int r = trial(k0, w0, (int64_t)(f * wmean))) return r;
+            if (int r = trial(kd, w0, (int64_t)(f * wmean))) return r;
         int64_t d0 = bv.delta;
         for (double f : {0.5, 2.0})
-            if (int r = trial(k0, w0, (int64_t)(f * d0))) return r;
+            if (int r = trial(kd, w0, (int64_t)(f * d0))) return r;
+        if (by_rounds && rest >= 16 * kd)
+            for (auto& kv : seen)
+                if (kv.second <= 1.2 * best && std::get<2>(kv.first) < bv.delta) bv.delta = std::get<2>(kv.first);
+    } else {
+        if (int r = trial(kd, w0, delta)) return r;
     }
-    // then workgroup size x threads in flight (trees in flight = threads /
-    // workgroup size) at that bucket width
-    {
+    if (!by_rounds && !o.wg_size)
         // (64 and 128 threads: one or two waves per tree, for graphs whose
         // main-phase trees are tiny)
-        const int wgs[5] = {64, 128, 256, 512, 1024};
-        for (int w : wgs) {
-            if (o.wg_size && w != wg) continue;
-            if (o.roots_in_flight) {
-                if (int r = trial(k, w, bv.delta)) return r;
-                continue;
-            }
-            for (int threads : {1 << 17, 1 << 18, 1 << 19, 1 << 20})
-                if (int r = trial(threads / w, w, bv.delta)) return r;
-        }
-    }
+        for (int w : {64, 128, 256, 512})
+            if (int r = trial(o.roots_in_flight ? k : fill(w), w, bv.delta)) return r;
     // time the two best settings once more and keep the faster in sum:
     // single trials of a few milliseconds are noisy
-    if (seen.size() >= 2) {
+    if (seen.size() >= 2 && !by_rounds) {
         std::vector<std::pair<double, std::tuple<int, int, int64_t>>> rank;
         for (auto& kv : seen) rank.push_back({kv.second, kv.first});
         std::sort(rank.begin(), rank.end());
@@ -1572,7 +1642,8 @@ static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_o
     }
     // then the small-tree kernel (trees in LDS, the batched kernel with the
     // setting found for the trees that do not fit), against the best setting
-    if (!o.small_trees && small_capacity(B.key_bits) > 0) {
+    // (its tables hold 128 vertices: not for trees that are larger on average)
+    if (!o.small_trees && avg_settled <= 128 && small_capacity(B.key_bits) > 0) {
         const int kk = std::max(1, std::min(bv.k, kmax));
         double ms_b = 0, ms_s = 0;
         if (int r = time_once(kk, bv.wg, bv.delta, ms_b)) return r;
@@ -1600,6 +1671,7 @@ static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_o
     wg = bv.wg;
     delta = bv.delta;
     if (!o.small_trees) small = bv.small;
+    bv.labels = labels;
     std::lock_guard<std::mutex> lk(g_tune_mu);
     g_tune[key] = bv;
     return 0;

@@ -105,6 +105,31 @@ int launch_stat_sums(int32_t n, const int64_t* stats, int64_t* sums, hipStream_t
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// Sums over cnt listed roots of the columns 0 (settled), 1 (arcs), 2 (labels)
+// and 4 (rounds).
+__global__ __launch_bounds__(256) void k_root_sums(int32_t cnt, const int32_t* __restrict__ roots,
+                                                   const int64_t* __restrict__ st,
+                                                   unsigned long long* __restrict__ sums) {
+    unsigned long long x[4] = {0, 0, 0, 0};
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += gridDim.x * blockDim.x) {
+        const int64_t* r = st + (int64_t)roots[i] * STAT_COLS;
+        x[0] += (unsigned long long)r[0];
+        x[1] += (unsigned long long)r[1];
+        x[2] += (unsigned long long)r[2];
+        x[3] += (unsigned long long)r[4];
+    }
+    for (int c = 0; c < 4; c++) {
+        for (int d = 32; d >= 1; d >>= 1) x[c] += __shfl_xor(x[c], d);
+        if ((threadIdx.x & 63) == 0 && x[c]) atomicAdd(&sums[c], x[c]);
+    }
+}
+
+int launch_root_sums(int32_t cnt, const int32_t* roots, const int64_t* stats, int64_t* sums, hipStream_t st) {
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(256, ((int64_t)cnt + 255) / 256));
+    hipLaunchKernelGGL(k_root_sums, dim3(grid), dim3(256), 0, st, cnt, roots, stats, (unsigned long long*)sums);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 // Roots among the rank positions [lo, lo + cnt) whose tree is the root
 // alone. A root r without arcs settles only itself; a root all of whose
 // neighbours outrank it (rank positions below r: the last arc of r's row,

@@ -272,6 +272,8 @@ int launch_level_order(const int64_t* poff, int32_t g, int32_t g2, int32_t partn
                        int64_t* off2, int32_t* roots, hipStream_t st);
 // assemble.hip: totals of the per-root statistics (settled, arcs, stopped
 // early) into sums[0..2] (zeroed by the caller)
+// sums[0..3] += settled, arcs, labels and rounds of cnt listed roots
+int launch_root_sums(int32_t cnt, const int32_t* roots, const int64_t* stats, int64_t* sums, hipStream_t st);
 int launch_stat_sums(int32_t n, const int64_t* stats, int64_t* sums, hipStream_t st);
 constexpr int PRUNE_HEAD = 4;          // prefix labels of a vertex that are tested first (32 bytes)
 constexpr int HASH_MIN_PREFIX = 4096;   // prefixes from this size hash the root's distances

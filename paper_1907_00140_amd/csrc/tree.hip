@@ -694,9 +694,14 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                     p.failed[atomicAdd(p.nfailed, 1)] = p.roots ? p.roots[c] : p.root_base + c;
                 S.bnext = S.bend;
             } else if (S.bnext >= S.bend) {
-                const int32_t c = atomicAdd(p.next_root, p.pop_batch);
+                // fewer while the queue is young: the first roots' trees are
+                // the largest, and the workgroup that held sixteen of them
+                // ended long after the others (512x512 grid: 305 ms of one
+                // launch)
+                const int32_t take = min(p.pop_batch, 1 + S.bend / (4 * (int32_t)gridDim.x));
+                const int32_t c = atomicAdd(p.next_root, take);
                 S.bnext = c;
-                S.bend = c < p.nroots ? min(p.nroots, c + p.pop_batch) : c;
+                S.bend = c < p.nroots ? min(p.nroots, c + take) : c;
             }
             if (S.bnext < S.bend) {
                 r = p.roots ? p.roots[S.bnext] : p.root_base + S.bnext;
