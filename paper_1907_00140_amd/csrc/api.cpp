@@ -141,6 +141,39 @@ HostCtl* host_ctl() {
     return lease.h;
 }
 
+}  // namespace
+
+// Error words of the labelings: pinned host memory that a kernel writes
+// directly when it meets an invalid id, so that a query needs neither a fill
+// before its kernel nor a copy behind it. Carved from blocks that live as long
+// as the process; a handle returns its word when it is freed.
+namespace chl {
+namespace {
+std::mutex g_ew_mu;
+std::vector<int32_t*> g_ew_free;
+}  // namespace
+int32_t* err_word_get() {
+    constexpr size_t WORDS = 1024;
+    std::lock_guard<std::mutex> lk(g_ew_mu);
+    if (g_ew_free.empty()) {
+        g_ew_free.reserve(WORDS);
+        int32_t* b = nullptr;
+        if (hipHostMalloc((void**)&b, WORDS * 4, hipHostMallocDefault) != hipSuccess) return nullptr;
+        for (size_t i = 0; i < WORDS; i++) g_ew_free.push_back(b + i);
+    }
+    int32_t* w = g_ew_free.back();
+    g_ew_free.pop_back();
+    return w;
+}
+void err_word_put(int32_t* w) {
+    if (!w) return;
+    std::lock_guard<std::mutex> lk(g_ew_mu);
+    g_ew_free.push_back(w);
+}
+}  // namespace chl
+
+namespace {
+
 // ---------------------------------------------------------------- tuning
 struct TuneKey {
     int32_t n;
@@ -674,16 +707,14 @@ int chl_query(const chl_labels* hc, const int32_t* pairs, int64_t q, int64_t* ou
     (void)hipGetLastError();
     // the error word is per handle: concurrent queries on one handle serialise here
     std::lock_guard<std::mutex> lk(h->qmu);
-    HIPCHK(hipMemsetAsync(h->qerr, 0, 4, st));
+    clear_err(h);
     double avg = h->n ? (double)h->total / h->n : 1.0;
     const bool dir = h->directed != 0;
     if (launch_query(h->n, h->offsets, h->hub_pos, h->dist, dir ? h->in_offsets : h->offsets,
                      dir ? h->in_hub_pos : h->hub_pos, dir ? h->in_dist : h->dist, pairs, q, out, h->qerr, avg, st))
         return CHL_ERR_HIP;
-    int32_t e = 0;
-    HIPCHK(hipMemcpyAsync(&e, h->qerr, 4, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    return e ? CHL_ERR_INVALID_ARG : CHL_OK;
+    return read_err(h) ? CHL_ERR_INVALID_ARG : CHL_OK;
 }
 
 int chl_build_stats(const chl_labels* h, chl_stats* totals, int64_t* per_root, int to_host, void* stream) {
@@ -707,7 +738,7 @@ void chl_labels_free(chl_labels* h) {
     f(h->dist);
     f(h->order);
     f(h->per_root);
-    f(h->qerr);
+    err_word_put(h->qerr);
     f(h->in_offsets);
     f(h->in_hub_pos);
     f(h->in_dist);
@@ -1436,10 +1467,12 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     L->hub_pos = keep.get<int32_t>(std::max<unsigned long long>(used, 1));
     L->dist = keep.get<int32_t>(std::max<unsigned long long>(used, 1));
     L->order = hub_order;
-    L->qerr = keep.get<int32_t>(4);
     if (A.oom || keep.oom) { delete L; return CHL_ERR_OOM; }
+    L->qerr = err_word_get();
+    if (!L->qerr) { delete L; return CHL_ERR_OOM; }
     if (launch_assemble(n, order, B.pool, used, count, L->offsets, fill, tmp, L->hub_pos, L->dist, scan_tmp,
                         nullptr, st)) {
+        err_word_put(L->qerr);
         delete L;
         return CHL_ERR_HIP;
     }
@@ -1452,6 +1485,7 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
             launch_stat_sums(n, B.stats, dsum, st) ||
             hipMemcpyAsync(hc->sums, dsum, 32, hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess) {
+            err_word_put(L->qerr);
             delete L;
             return CHL_ERR_HIP;
         }

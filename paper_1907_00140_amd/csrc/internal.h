@@ -306,8 +306,20 @@ struct chl_labels {
     int32_t* in_dist = nullptr;
     int32_t* order = nullptr;     // [n] = hub_vertex
     int64_t* per_root = nullptr;  // [n][4] or null
-    int32_t* qerr = nullptr;      // query error word
+    int32_t* qerr = nullptr;      // query error word (err_word_get)
     chl_stats st{};
     chl_allocator alloc{};
     std::mutex qmu;
 };
+
+namespace chl {
+// Pinned host words that kernels set (never clear) through a plain store;
+// nullptr when no memory is left.
+int32_t* err_word_get();
+void err_word_put(int32_t* w);
+inline void clear_err(chl_labels* h) { *(volatile int32_t*)h->qerr = 0; }
+inline int32_t read_err(const chl_labels* h) { return *(volatile int32_t*)h->qerr; }   // after the stream's synchronisation
+#ifdef __HIPCC__
+__device__ __forceinline__ void set_invalid(int32_t* err) { *(volatile int32_t*)err = ERR_BIT_INVALID; }
+#endif
+}  // namespace chl

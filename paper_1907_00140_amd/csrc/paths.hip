@@ -116,7 +116,7 @@ __device__ __forceinline__ void parents_of(const ParentArgs& a, int32_t v, Label
     const int64_t lb = a.off[v], le = a.off[v + 1];
     int64_t eb = a.row[v], ee = a.row[v + 1];
     if (eb < 0 || ee < eb || ee > a.m) {          // malformed row: no arcs, flagged
-        if (gl == 0) atomicOr(a.err, ERR_BIT_INVALID);
+        if (gl == 0) set_invalid(a.err);
         eb = ee = 0;
     }
     for (int64_t c0 = lb; c0 < le; c0 += PCH) {
@@ -146,7 +146,7 @@ __device__ __forceinline__ void parents_of(const ParentArgs& a, int32_t v, Label
                     if (end > beg && a.hub[end - 1] > hhi) end = lower_hub(a.hub, beg, end, hhi + 1);
                     len = end - beg;
                 } else {
-                    atomicOr(a.err, ERR_BIT_INVALID);
+                    set_invalid(a.err);
                 }
             }
             int64_t inc = len;
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(64 * PW) void k_parents(ParentArgs a, const int32_t
     for (int64_t idx = (int64_t)blockIdx.x * PW + w; idx < a.n; idx += (int64_t)gridDim.x * PW) {
         const int32_t v = vorder[idx];
         if (v < 0 || v >= a.n) {
-            if (lane == 0) atomicOr(a.err, ERR_BIT_INVALID);
+            if (lane == 0) set_invalid(a.err);
             continue;
         }
         if (a.row[v + 1] - a.row[v] > HEAVY_ARCS) continue;      // k_parents_heavy
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(256) void k_path(int32_t n, const int64_t* __restri
             if (!WRITE && gl == 0) {
                 hops[k] = ok ? -1 : -2;
                 if (len) len[k] = 0;
-                if (!ok) atomicOr(err, ERR_BIT_INVALID);
+                if (!ok) set_invalid(err);
             }
             continue;
         }
@@ -329,11 +329,11 @@ __global__ __launch_bounds__(256) void k_path(int32_t n, const int64_t* __restri
         const int bad_any = __shfl_xor((int)bad, 1, G) | (int)bad;
         if (gl == 0) {
             if (WRITE) {
-                if (bad_any || path_off[k + 1] - path_off[k] != chain + other + 1) atomicOr(err, ERR_BIT_INVALID);
+                if (bad_any || path_off[k + 1] - path_off[k] != chain + other + 1) set_invalid(err);
             } else {
                 hops[k] = bad_any ? -2 : chain + other;
                 if (len) len[k] = bad_any ? 0 : chain + other + 1;
-                if (bad_any) atomicOr(err, ERR_BIT_INVALID);
+                if (bad_any) set_invalid(err);
             }
         }
     }
@@ -369,13 +369,11 @@ template <typename F>
 int with_err(const chl_labels* hc, hipStream_t st, F f) {
     chl_labels* h = const_cast<chl_labels*>(hc);
     std::lock_guard<std::mutex> lk(h->qmu);
-    if (hipMemsetAsync(h->qerr, 0, 4, st) != hipSuccess) return CHL_ERR_HIP;
+    clear_err(h);
     const int rc = f();
     if (rc) return rc;
-    int32_t e = 0;
-    if (hipMemcpyAsync(&e, h->qerr, 4, hipMemcpyDeviceToHost, st) != hipSuccess) return CHL_ERR_HIP;
     if (hipStreamSynchronize(st) != hipSuccess) return CHL_ERR_HIP;
-    return e ? CHL_ERR_INVALID_ARG : CHL_OK;
+    return read_err(h) ? CHL_ERR_INVALID_ARG : CHL_OK;
 }
 
 }  // namespace

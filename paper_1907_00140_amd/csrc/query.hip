@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) void k_query_tier(int32_t n, const int64_t* __
                     big = true;
                 }
             } else {
-                atomicOr(err, ERR_BIT_INVALID);
+                set_invalid(err);
                 out[k] = -2;
             }
         }
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void k_query_hash(int32_t n, const int64_t* __
                 }
             }
         } else if (gl == 0) {
-            atomicOr(err, ERR_BIT_INVALID);
+            set_invalid(err);
         }
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) {
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(256) void k_query_group(int32_t n, const int64_t* _
                 }
             }
         } else if (gl == 0) {
-            atomicOr(err, ERR_BIT_INVALID);
+            set_invalid(err);
         }
 #pragma unroll
         for (int d = G / 2; d >= 1; d >>= 1) {
