@@ -1470,8 +1470,11 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     if (A.oom || keep.oom) { delete L; return CHL_ERR_OOM; }
     L->qerr = err_word_get();
     if (!L->qerr) { delete L; return CHL_ERR_OOM; }
-    if (launch_assemble(n, order, B.pool, used, count, L->offsets, fill, tmp, L->hub_pos, L->dist, scan_tmp,
-                        nullptr, st)) {
+    // the pruning levels' labels are grouped already (a root subset has
+    // dropped them, and the Hybrid's cleaning has moved the pool)
+    const bool groups = o.mode == CHL_MODE_BATCHED && o.root_count == 0 && o.hybrid_psi == 0 && B.poff && B.plab_hub;
+    if (launch_assemble(n, order, B.pool, used, groups ? B.cursor_base : 0, B.poff, B.plab_hub, count, L->offsets,
+                        fill, tmp, L->hub_pos, L->dist, scan_tmp, st)) {
         err_word_put(L->qerr);
         delete L;
         return CHL_ERR_HIP;

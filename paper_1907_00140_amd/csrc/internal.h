@@ -217,10 +217,9 @@ int launch_tree_group(const TreeParams& p, int key_bits, int wg, int team_size, 
 int group_capacity(int key_bits, int pbound);   // co-resident workgroups of the group kernel
 
 // assemble.hip
-int launch_assemble(int32_t n, const int32_t* order, const Pool& pool, uint64_t total,
-                    int32_t* count, int64_t* offsets, int32_t* fill, uint64_t* tmp,
-                    int32_t* hub_pos, int32_t* dist, void* scan_temp, void* sort_temp,
-                    hipStream_t st);
+int launch_assemble(int32_t n, const int32_t* order, const Pool& pool, uint64_t total, uint64_t grouped,
+                    const int64_t* off_old, const uint64_t* lab_old, int32_t* count, int64_t* offsets, int32_t* fill,
+                    uint64_t* tmp, int32_t* hub_pos, int32_t* dist, void* scan_temp, hipStream_t st);
 
 // assemble.hip: the labels of the pool entries [0, used) grouped by vertex
 // (rank position), as (hub << 32) | dist words, from the groups of the
