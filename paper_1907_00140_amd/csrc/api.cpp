@@ -145,20 +145,25 @@ HostCtl* host_ctl() {
 
 // Error words of the labelings: pinned host memory that a kernel writes
 // directly when it meets an invalid id, so that a query needs neither a fill
-// before its kernel nor a copy behind it. Carved from blocks that live as long
-// as the process; a handle returns its word when it is freed.
+// before its kernel nor a copy behind it. Portable: a handle may live on any of
+// the process's devices. Carved from blocks that live as long as the process
+// (4 KB per 1024 handles alive at once); a handle returns its word when freed.
 namespace chl {
 namespace {
 std::mutex g_ew_mu;
 std::vector<int32_t*> g_ew_free;
+size_t g_ew_words = 0;
 }  // namespace
 int32_t* err_word_get() {
     constexpr size_t WORDS = 1024;
     std::lock_guard<std::mutex> lk(g_ew_mu);
     if (g_ew_free.empty()) {
-        g_ew_free.reserve(WORDS);
+        g_ew_free.reserve(g_ew_words + WORDS);   // room for every word: err_word_put never allocates
         int32_t* b = nullptr;
-        if (hipHostMalloc((void**)&b, WORDS * 4, hipHostMallocDefault) != hipSuccess) return nullptr;
+        if (hipHostMalloc((void**)&b, WORDS * 4,
+                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+            return nullptr;
+        g_ew_words += WORDS;
         for (size_t i = 0; i < WORDS; i++) g_ew_free.push_back(b + i);
     }
     int32_t* w = g_ew_free.back();
