@@ -795,7 +795,7 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
     Slots s1{};
     if (int r = alloc_slots(A, B, kpre, s1, st)) return r;
     HIPCHK(hipMemsetAsync(B.ctl64, 0, 8, st));
-    auto regroup = [&]() -> int {
+    auto regroup = [&](int32_t hubs) -> int {      // hubs: the roots so far
         const unsigned long long used = B.last_used;
         const int nx = cur < 0 ? 0 : 1 - cur;
         if (used > plab_cap[nx]) {
@@ -822,7 +822,7 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
             if (!byd) return CHL_ERR_OOM;
         }
         if (launch_swap_halves(plab[cur], byd, used, st) ||
-            launch_segsort_u64(byd, poff[cur], n, (int64_t)used, nullptr, st) ||
+            launch_segsort_u64(byd, poff[cur], n, (int64_t)used, hubs, st) ||
             launch_group_heads(n, poff[cur], byd, B.head, st))
             return CHL_ERR_HIP;
         B.plab = byd;
@@ -910,7 +910,7 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
     if (int r = run_batched(A, B, s1, lwg, dl, o.early_term, nullptr, g, st, &launches, 2, 0, tcp0, false, gcp0))
         return r;
     B.record_level(g, B.kernel_ms - ms0, gcp0 ? -gcp0->size : tcp0 ? tcp0->size : 1);
-    if (int r = regroup()) return r;
+    if (int r = regroup(g)) return r;
     unsigned long long level_labels = B.cursor_base;
     grown = g;
     bool probed = false;
@@ -998,7 +998,7 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
                                     ordered, gcp))
                 return r;
             B.record_level(g2, B.kernel_ms - ms1, gcp ? -gcp->size : tcp ? tcp->size : 1);
-            if (int r = regroup()) return r;
+            if (int r = regroup(g2)) return r;
             level_labels = B.cursor_base - before;
             g = g2;
         }
@@ -1133,7 +1133,7 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
             if (!byd) return CHL_ERR_OOM;
         }
         if (launch_swap_halves(tlab[cur], byd, grouped, st) ||
-            launch_segsort_u64(byd, toff[cur], n, (int64_t)grouped, nullptr, st) ||
+            launch_segsort_u64(byd, toff[cur], n, (int64_t)grouped, n, st) ||
             launch_group_heads(n, toff[cur], byd, B.head, st))
             return CHL_ERR_HIP;
         B.poff = toff[cur];
@@ -1263,7 +1263,7 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     if (launch_rank_degrees(n, g->row_ptr, order, rdeg, st)) return CHL_ERR_HIP;
     if (launch_scan_i64(rdeg, rrow, n, scan_tmp, st)) return CHL_ERR_HIP;
     if (launch_renumber(n, B.m, g->row_ptr, g->col, g->w, order, pos, rrow, rarc, st)) return CHL_ERR_HIP;
-    if (launch_segsort_u64(rarc, rrow, n, B.m, nullptr, st)) return CHL_ERR_HIP;
+    if (launch_segsort_u64(rarc, rrow, n, B.m, B.m, st)) return CHL_ERR_HIP;
     if (!directed && launch_check_symmetric(n, B.m, rrow, rarc, err, st)) return CHL_ERR_HIP;
     HIPCHK(hipMemcpyAsync(hub_order, order, (size_t)n * 4, hipMemcpyDeviceToDevice, st));
     // the tuner caches' input signature is sampled here (the input is valid),

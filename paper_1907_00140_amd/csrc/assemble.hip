@@ -107,7 +107,7 @@ int launch_assemble(int32_t n, const int32_t* order, const Pool& pool, uint64_t 
         hipLaunchKernelGGL(k_scatter, dim3(g(add)), dim3(256), 0, st, pool.v + grouped, pool.hub + grouped,
                            pool.dist + grouped, add, order, offsets, fill, tmp);
     if (total > 0) {
-        if (launch_segsort_u64(tmp, offsets, n, (int64_t)total, nullptr, st)) return -1;
+        if (launch_segsort_u64(tmp, offsets, n, (int64_t)total, n, st)) return -1;
         hipLaunchKernelGGL(k_split, dim3(g(total)), dim3(256), 0, st, tmp, total, hub_pos, dist);
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;
@@ -269,7 +269,7 @@ int launch_level_order(const int64_t* poff, int32_t g, int32_t g2, int32_t partn
     if (nr <= 0) return 0;
     const int blocks = (nr + 255) / 256 < 1024 ? (nr + 255) / 256 : 1024;
     hipLaunchKernelGGL(k_level_keys, dim3(blocks), dim3(256), 0, st, poff, g, g2, partner, keys, off2);
-    if (launch_segsort_u64(keys, off2, 1, nr, nullptr, st)) return -1;
+    if (launch_segsort_u64(keys, off2, 1, nr, nr, st)) return -1;
     hipLaunchKernelGGL(k_level_roots, dim3(blocks), dim3(256), 0, st, keys, nr, roots);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

@@ -176,10 +176,11 @@ size_t scan_temp_bytes(int64_t n);
 int launch_scan_i64(const int64_t* in, int64_t* out, int64_t n, void* temp, hipStream_t st);
 int launch_scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, void* temp, hipStream_t st);
 
-// segsort.hip: sort every segment [off[i], off[i+1]) of keys ascending
+// segsort.hip: sort every segment [off[i], off[i+1]) of keys ascending; no
+// segment is longer than max_len
 size_t segsort_temp_bytes(int64_t nseg);
 int launch_segsort_u64(uint64_t* keys, const int64_t* off, int64_t nseg, int64_t total,
-                       void* temp, hipStream_t st);
+                       int64_t max_len, hipStream_t st);
 
 // tree.hip
 // phase: 0 main phase of a build, 1 autotuner probe, 2 common-label roots

@@ -310,7 +310,7 @@ int launch_transpose(int32_t n, int64_t m, const int64_t* row, const int32_t* co
     if (m > 0) {
         hipLaunchKernelGGL(k_tscatter, dim3(grid_for((int64_t)n * 64, 256)), dim3(256), 0, st, n, row, col, w,
                            cursor, tkey);
-        if (launch_segsort_u64(tkey, trow, n, m, nullptr, st)) return -1;
+        if (launch_segsort_u64(tkey, trow, n, m, m, st)) return -1;
         hipLaunchKernelGGL(k_tsplit, dim3(grid_for(m, 256)), dim3(256), 0, st, m, tkey, tcol, tw);
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;

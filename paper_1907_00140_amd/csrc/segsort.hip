@@ -18,6 +18,7 @@ namespace chl {
 
 namespace {
 
+constexpr int WCAP = 256;
 constexpr int LCAP = 8192;
 constexpr int BLK = 256;
 constexpr int BLKL = 1024;
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(BLKL) void k_sort_lds(uint64_t* __restrict__ keys,
             const int64_t s = (int64_t)blockIdx.x + G * (i0 + threadIdx.x);
             if (s < nseg) {
                 const int64_t l = off[s + 1] - off[s];
-                if (l > 256 && l <= LCAP) lst[atomicAdd(&cnt, 1)] = s;
+                if (l > WCAP && l <= LCAP) lst[atomicAdd(&cnt, 1)] = s;
             }
         }
         __syncthreads();
@@ -214,12 +215,18 @@ int grid_cap(int64_t work) {
 
 size_t segsort_temp_bytes(int64_t) { return 0; }
 
-int launch_segsort_u64(uint64_t* keys, const int64_t* off, int64_t nseg, int64_t total, void*,
+// A tier whose lengths no segment can have is not launched: it would only look
+// through the offsets. A label list is at most as long as there are hubs, so
+// the first levels take one tier (what it gives is measured with the scans').
+int launch_segsort_u64(uint64_t* keys, const int64_t* off, int64_t nseg, int64_t total, int64_t max_len,
                        hipStream_t st) {
     if (nseg <= 0 || total <= 1) return 0;
+    if (max_len > total) max_len = total;
     hipLaunchKernelGGL(k_sort_wave, dim3(grid_cap((nseg + 3) / 4)), dim3(BLK), 0, st, keys, off, nseg);
-    hipLaunchKernelGGL(k_sort_lds, dim3(grid_cap(nseg < 2048 ? nseg : 2048)), dim3(BLKL), 0, st, keys, off, nseg);
-    hipLaunchKernelGGL(k_sort_global, dim3(grid_cap(nseg < 1024 ? nseg : 1024)), dim3(BLKG), 0, st, keys, off, nseg);
+    if (max_len > WCAP)
+        hipLaunchKernelGGL(k_sort_lds, dim3(grid_cap(nseg < 2048 ? nseg : 2048)), dim3(BLKL), 0, st, keys, off, nseg);
+    if (max_len > LCAP)
+        hipLaunchKernelGGL(k_sort_global, dim3(grid_cap(nseg < 1024 ? nseg : 1024)), dim3(BLKG), 0, st, keys, off, nseg);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
