@@ -1277,8 +1277,7 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     if (launch_sample_gaps(n, g->row_ptr, g->col, gap, near, st)) return CHL_ERR_HIP;
     HIPCHK(hipMemcpyAsync(hc0->c32, err, 20, hipMemcpyDeviceToHost, st));
     tprep.record_end();
-    // 32-bit keys are exact when no simple path can reach 2^31 - 1
-    B.key_bits = ((double)(n - 1) * (double)B.maxw <= 2147483646.0) ? 32 : 64;
+    B.key_bits = key_bits_for(n, B.maxw);
     S.key_bits = B.key_bits;
 
     // the build's buffers are taken while the renumbering runs

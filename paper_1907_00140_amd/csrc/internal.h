@@ -21,6 +21,18 @@ template <typename K> struct KeyTraits;
 template <> struct KeyTraits<uint32_t> { static constexpr uint32_t INF = 0xFFFFFFFFu; };
 template <> struct KeyTraits<uint64_t> { static constexpr uint64_t INF = ~0ull; };
 
+template <typename K>
+__host__ __device__ __forceinline__ K pack(uint64_t d, uint32_t clean) { return (K)((d << 1) | clean); }
+
+// Key width of a graph: 32 bits if every candidate fits. A key holds the
+// length of a simple path, at most (n - 1) * maxw, but the arcs that lead back
+// from its end are relaxed too, so a candidate reaches n * maxw; one that
+// wrapped around would look like an improvement. (2^31 - 2 is the largest
+// distance of a 32-bit key, 2^31 - 1 with the clean bit reads as not reached.)
+inline int key_bits_for(int32_t n, int32_t maxw) {
+    return (uint64_t)n * (uint64_t)maxw <= 2147483646ull ? 32 : 64;
+}
+
 // per-root statistics columns: vertex relaxations, arcs relaxed, labels,
 // stopped early, relaxation rounds, device wall-clock ticks of the tree
 constexpr int STAT_COLS = 6;

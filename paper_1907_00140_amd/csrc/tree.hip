@@ -109,9 +109,6 @@ __device__ __forceinline__ T block_reduce(T x, T* red, T ident, F op) {
     return r;
 }
 
-template <typename K>
-__device__ __forceinline__ K pack(uint64_t d, uint32_t clean) { return (K)((d << 1) | clean); }
-
 // LDS of the block-level frontier expansion.
 template <typename K, int WG>
 struct Expand {
