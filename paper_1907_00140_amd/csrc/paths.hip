@@ -107,6 +107,14 @@ struct ParentArgs {
     int32_t* err;
 };
 
+// A valid row of more than HEAVY_ARCS arcs, which k_parents leaves to
+// k_parents_heavy; every other row, malformed ones among them, is k_parents',
+// which flags those whatever their length.
+__device__ __forceinline__ bool heavy_row(const ParentArgs& a, int32_t v) {
+    const int64_t b = a.row[v], e = a.row[v + 1];
+    return b >= 0 && b <= e && e <= a.m && e - b > HEAVY_ARCS;
+}
+
 // Parents of v's labels by W waves (W = 1, or a whole workgroup).
 template <int W>
 __device__ __forceinline__ void parents_of(const ParentArgs& a, int32_t v, LabelLds& S, ArcLds& R) {
@@ -201,7 +209,7 @@ __global__ __launch_bounds__(64 * PW) void k_parents(ParentArgs a, const int32_t
             if (lane == 0) set_invalid(a.err);
             continue;
         }
-        if (a.row[v + 1] - a.row[v] > HEAVY_ARCS) continue;      // k_parents_heavy
+        if (heavy_row(a, v)) continue;
         parents_of<1>(a, v, S[w], R[w]);
     }
 }
@@ -221,7 +229,7 @@ __global__ __launch_bounds__(64 * HW) void k_parents_heavy(ParentArgs a, const i
         const int64_t i = i0 + (int64_t)threadIdx.x * gridDim.x;
         if (i < a.n) {
             const int32_t v = vorder[i];
-            if (v >= 0 && v < a.n && a.row[v + 1] - a.row[v] > HEAVY_ARCS) list[atomicAdd(&count, 1)] = v;
+            if (v >= 0 && v < a.n && heavy_row(a, v)) list[atomicAdd(&count, 1)] = v;
         }
         __syncthreads();
         const int32_t c = count;
@@ -397,7 +405,7 @@ extern "C" int chl_labels_parents(const chl_labels* h, const chl_graph* g, int32
         // (the heavy vertices first: the others fill the device beside the
         // last of them)
         const int64_t hblocks = std::max<int64_t>(1, std::min<int64_t>(h->n, 512));
-        if (g->n_arcs > HEAVY_ARCS)
+        if (g->n_arcs > HEAVY_ARCS)      // (else no valid row is heavy)
             hipLaunchKernelGGL(k_parents_heavy, dim3(hblocks), dim3(64 * HW), 0, st, a, h->order);
         hipLaunchKernelGGL(k_parents, dim3(blocks), dim3(64 * PW), 0, st, a, h->order);
         return hipGetLastError() == hipSuccess ? CHL_OK : CHL_ERR_HIP;
