@@ -372,15 +372,17 @@ int launch_path(const chl_labels* h, const int32_t* parent, const int32_t* slot,
 }
 
 // clear the handle's error word, run f, read the word back (the word is per
-// handle: calls on one handle serialise here)
+// handle: calls on one handle serialise here). Waits for the stream also when
+// f failed: its first launches may be running, on the caller's arrays.
 template <typename F>
 int with_err(const chl_labels* hc, hipStream_t st, F f) {
     chl_labels* h = const_cast<chl_labels*>(hc);
     std::lock_guard<std::mutex> lk(h->qmu);
     clear_err(h);
     const int rc = f();
+    const bool done = hipStreamSynchronize(st) == hipSuccess;
     if (rc) return rc;
-    if (hipStreamSynchronize(st) != hipSuccess) return CHL_ERR_HIP;
+    if (!done) return CHL_ERR_HIP;
     return read_err(h) ? CHL_ERR_INVALID_ARG : CHL_OK;
 }
 
@@ -440,8 +442,7 @@ extern "C" int chl_query_path_hops(const chl_labels* h, const int32_t* parent, c
         return CHL_OK;
     });
     if (len) {
-        // the stream has been synchronised by with_err (or the launch failed)
-        (void)hipStreamSynchronize(st);
+        // (with_err has waited for the stream)
         h->alloc.free(len, h->alloc.ctx);
         h->alloc.free(temp, h->alloc.ctx);
     }
