@@ -227,6 +227,9 @@ __global__ __launch_bounds__(256) void k_query_hash(int32_t n, const int64_t* __
                             best = sum < best ? sum : best;
                         }
                 }
+                // every lookup is done before the table is cleared again (with
+                // four waves the barriers of the reduction see to that)
+                if (NWV == 1) sync();
             } else {
                 for (int64_t i = ab + gl; i < ae; i += GS) {
                     const int32_t x = ha[i];
@@ -246,7 +249,6 @@ __global__ __launch_bounds__(256) void k_query_hash(int32_t n, const int64_t* __
             best = o < best ? o : best;
         }
         if (NWV > 1) {
-            // (also: every lookup is done before the table is cleared again)
             if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
             __syncthreads();
 #pragma unroll
