@@ -180,14 +180,22 @@ void err_word_put(int32_t* w) {
 namespace {
 
 // ---------------------------------------------------------------- tuning
+// A setting that the caller fixed is part of the key: what was tuned around it
+// (four trees in flight, say, where a server caps them) is not what an
+// unrestricted build of the same graph would find.
 struct TuneKey {
     int32_t n;
     int64_t m;
     int32_t maxw;
-    int mode;
     uint64_t sig;
+    int32_t early;
+    // tuner only
+    int32_t hybrid = 0, grown = 0, pbound = 0;      // schedule
+    int32_t k = 0, wg = 0, small = 0;               // settings of the caller, 0: free
+    int64_t delta = 0;
     bool operator<(const TuneKey& o) const {
-        return std::tie(n, m, maxw, mode, sig) < std::tie(o.n, o.m, o.maxw, o.mode, o.sig);
+        return std::tie(n, m, maxw, sig, early, hybrid, grown, pbound, k, wg, small, delta) <
+               std::tie(o.n, o.m, o.maxw, o.sig, o.early, o.hybrid, o.grown, o.pbound, o.k, o.wg, o.small, o.delta);
     }
 };
 struct TuneVal {
@@ -246,6 +254,10 @@ struct Build {
         if (nlev < CHL_MAX_LEVELS) { lv_end[nlev] = end; lv_ms[nlev] = ms; lv_team[nlev] = team; nlev++; }
     }
 };
+
+TuneKey graph_key(const Build& B, const chl_build_opts& o) {
+    return TuneKey{B.n, B.m, B.maxw, B.sig, o.early_term != 0};
+}
 
 // labels emitted by a pruning level above which the next level is only
 // two or four times as large (else eight times)
@@ -915,7 +927,7 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
     grown = g;
     bool probed = false;
     bool keep = o.prune_hubs > 0 || !o.autotune;
-    const TuneKey pkey{n, B.m, B.maxw, -1, B.sig};
+    const TuneKey pkey = graph_key(B, o);
     if (!keep) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_prune_keep.find(pkey);
@@ -1320,7 +1332,7 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     bool known_unpruned = false;
     if (o.prune_hubs == 0 && o.autotune) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        auto it = g_prune_keep.find(TuneKey{n, B.m, B.maxw, -1, B.sig});
+        auto it = g_prune_keep.find(graph_key(B, o));
         known_unpruned = it != g_prune_keep.end() && !it->second;
     }
     // (the levels' end is only recorded: the main phase's set-up is queued
@@ -1532,7 +1544,14 @@ static int pick_params(Arena& A, Build& B, const chl_graph* g, const chl_build_o
     if (!need) return 0;
     // (unpruned builds share one entry whether or not their first roots ran
     // as a level)
-    TuneKey key{n, B.m, B.maxw, ((o.hybrid_psi > 0 ? 2 : o.mode) * 8192 + (B.pbound ? B.grown : 0)) * 8192 + B.pbound, B.sig};
+    TuneKey key = graph_key(B, o);
+    key.hybrid = o.hybrid_psi > 0;
+    key.grown = B.pbound ? B.grown : 0;
+    key.pbound = B.pbound;
+    key.k = o.roots_in_flight;
+    key.wg = o.wg_size;
+    key.small = o.small_trees;
+    key.delta = o.delta;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune.find(key);
