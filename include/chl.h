@@ -164,7 +164,10 @@ typedef struct chl_build_opts {
                                 root). The main phase grows PLaNT trees in
                                 windows of consecutive roots, the first of
                                 r = max(64, n / 64) roots, each next one twice
-                                as large up to max(r, 8 * roots_in_flight);
+                                as large, up to min(max(n / 8, 1024),
+                                8 * roots_in_flight) but no less than r, or
+                                half as large (but no less than r) once Psi is
+                                past Psi_th / 2;
                                 once the vertex relaxations per label (Psi,
                                 Section 4.2.1) of a window's last r trees
                                 exceed Psi_th, the remaining roots grow as

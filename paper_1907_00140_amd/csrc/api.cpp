@@ -1055,11 +1055,21 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
     }
     std::vector<int64_t> rows;
     // Psi is taken over the last n/64 roots (at least 64) of a window, the
-    // most recent trees; the first window holds that many roots and each
-    // next one twice as many, up to 8 trees per slot, so that the switch
-    // point is resolved finely early on and the slots stay busy later
+    // most recent trees. The first window holds that many roots and each next
+    // one twice as many, while Psi is below half the threshold, and half as
+    // many above it. A window ends with its largest trees alone on the device,
+    // so it should be long; but the switch is seen at its end only, so it is
+    // bounded by the graph, n/8 roots (and, under 1024, by what keeps the
+    // workgroups busy twice over), not by the slots, of which there may be so
+    // many that one window holds half the graph. R-MAT 15 under a random
+    // ranking, threshold 100, crossed at root 18,547: windows up to 8 roots a
+    // slot switched at 32,256 (Psi 216), 141 ms; these at 19,968 (146), 137;
+    // n/16 throughout 142, n/32 at 18,944 (111) 152. R-MAT 16, crossed at
+    // 41,325: 48,128 (268), 704 ms; these 44,032 (153), 714; n/32 41,984 (121),
+    // 759.
     const int64_t recent = std::max<int64_t>(64, n / 64);
-    const int64_t wmax = std::max<int64_t>(recent, 8 * (int64_t)s.k);
+    const int64_t wmax =
+        std::max<int64_t>(recent, std::min<int64_t>(std::max<int64_t>(n / 8, 1024), 8 * (int64_t)s.k));
     int64_t win = recent;
     S.hybrid_switch = n;
     while (lo < n) {
@@ -1081,7 +1091,7 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
             S.hybrid_psi = psi;
             break;
         }
-        win = std::min<int64_t>(wmax, 2 * win);
+        win = 2 * psi > (double)o.hybrid_psi ? std::max<int64_t>(recent, win / 2) : std::min<int64_t>(wmax, 2 * win);
     }
     if (lo >= n) {
         if (own_stats) { A.drop(own_stats); B.stats = nullptr; }
