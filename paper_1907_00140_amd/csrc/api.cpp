@@ -779,10 +779,11 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
     const double wm = 0.5 * (1.0 + B.maxw);
     // default prefix: n/64 hubs, at least 64, at most 8192: each level
     // adds latency, each prefix hub saves work in every later tree, and
-    // there are more later trees on larger graphs (R-MAT 16: 1024 hubs
-    // build 4% faster than 4096; R-MAT 20: 4096 run the main phase 2.8x
-    // faster than 2048, and 8192 in 18.2 ms instead of 32.7, for a last
-    // level [2048, 8192) of 9.4 ms instead of [2048, 4096) of 3.7)
+    // there are more later trees on larger graphs (R-MAT 20: 2048, 4096
+    // and 8192 hubs run the main phase in 44.8, 19.3 and 7.9 ms for levels
+    // of 0, 3.0 and 7.2 ms beyond 2048, builds 131.7, 111.4 and 104.5 ms;
+    // R-MAT 16 builds in 5.55, 5.63, 5.80 and 6.11 ms with 512, 1024, 2048
+    // and 4096, directed in 7.49, 7.35 and 7.88 with 512, 2048 and 4096)
     const int32_t gdef = std::min<int32_t>(MAX_PREFIX, std::max<int32_t>(64, n / 64));
     const int32_t gmax = std::min<int32_t>(o.prune_hubs > 0 ? o.prune_hubs : gdef, n / 2);
     // prefix labels grouped by vertex, double-buffered: each level's
@@ -826,7 +827,7 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
         B.cursor_base = used;
         // the kernels read the groups ordered by distance (a pruning test
         // stops at the first entry that cannot give a shorter walk); the
-        // groups in hub order stay for the next extension
+        // groups as extended (in no order) stay for the next extension
         if (used > byd_cap) {
             if (byd) A.drop(byd);
             byd_cap = std::max<size_t>(used, 2 * byd_cap);
@@ -844,13 +845,15 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
     int32_t g = std::min<int32_t>(16, gmax);
     // the first levels hold the largest trees: 1024-thread workgroups,
     // teams of them for the narrow levels. Buckets of a quarter of the
-    // mean weight for the unpruned trees of level 0 (wider ones cost
-    // re-relaxation: R-MAT 20's level 0 relaxes 3.85x the oracle's arcs
-    // at half the mean weight, 3.6x at a quarter; narrower ones cost more
-    // team barriers than they save: an eighth relaxes 3.2x and takes as
-    // long, a sixteenth 2.6x and takes longer), twice the mean weight for
-    // the pruned levels, whose trees are smaller and latency bound
-    // (measured on R-MAT scales 16 and 20)
+    // mean weight for the unpruned trees of level 0: wider ones cost
+    // re-relaxation, narrower ones more team barriers than they save
+    // (R-MAT 20's level 0 relaxes 3.85x the oracle's arcs at half the mean
+    // weight, 3.6x at a quarter, 3.2x at an eighth, 2.6x at a sixteenth;
+    // at 1, 1/2, 1/4, 1/8 and 1/16 it takes 13.9, 12.7, 12.1, 12.2 and
+    // 14.1 ms, R-MAT 16's 1.35, 1.28, 1.26, 1.35 and 1.74); twice the mean
+    // weight for the pruned levels, whose trees are smaller and latency
+    // bound (R-MAT 16 builds at 1/2, 1, 2, 4 and 8: 5.98, 5.69, 5.63, 5.69
+    // and 5.70 ms; R-MAT 20 within 2%)
     const int64_t dl = std::max<int64_t>(1, (int64_t)(wm / 4));
     const int64_t dl1 = std::max<int64_t>(1, (int64_t)(2 * wm));
     // levels with fewer trees than the device holds workgroups of that
@@ -888,12 +891,15 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
     // Levels of 64 to 256 trees run as groups of GROUP_TREES trees with
     // vertex-major keys (the trees of a level reach largely the same
     // vertices), when the groups' state fits GROUP_MAX_BYTES. Measured on
-    // R-MAT 20 against one tree per team: levels [64,128), [128,256) and
-    // [256,512) take 26.8, 32.4 and 26.1 ms instead of 32.0, 44.6 and 38.6;
-    // the levels of 16 and 32 trees, whose few groups span 128 to 256
-    // workgroups each, are slower as groups (their hubs land on one workgroup
-    // for all 16 trees, and every round's barrier has 128-256 members), and
-    // so are levels of 512 trees, which share few vertices. The group
+    // R-MAT 20 against one tree per team (or workgroup): [32,128) takes 14.8
+    // ms instead of 25.4, [128,256) 12.3 instead of 13.5, and under factors
+    // of 2 [64,128) 8.9 instead of 12.0 and [256,512) 10.1 instead of 13.5;
+    // the levels of 16 trees, whose one group spans 256 workgroups, are
+    // slower as groups ([0,16) 56.9 instead of 12.1, [16,32) 5.9 instead of
+    // 4.7: their hubs land on one workgroup for all 16 trees, and every
+    // round's barrier has 256 members; 32 trees 6.3 instead of 7.0), and so
+    // are levels of 512 trees and more, which share few vertices ([512,1024)
+    // 13.4 instead of 9.8, [256,1024) 31.8 instead of 19.6). The group
     // buffers are kept across levels and grown when a level needs more.
     GroupCfg gcfg;
     const bool groups_on = o.group_levels >= 0 && o.team_wgs != 1 && lwg == 1024;
@@ -971,16 +977,17 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
             // a level whose trees emitted many labels did much work: grow
             // the prefix slowly, so that the next level is pruned by more
             // hubs, by 2 and 4 in turn (every level also costs a regrouping
-            // of the table and a launch tail: on R-MAT 20, 2, 4, 2, 4, 2
-            // built 3.5% faster than 2 throughout; 4 throughout, or 4 first,
-            // was slower); after a small level, whose time is the latency of
-            // its trees, grow by 8, to have fewer levels (the labels of a
-            // root do not depend on the schedule, so neither does the
-            // schedule itself). The first pruned level of a directed build
-            // grows by 4: its combined graph's second level [16, 128) ends
-            // with a few large trees on small teams, and [16, 64) on teams
-            // of 5 builds the directed R-MAT 16 5% faster (the undirected
-            // R-MAT 16 is 7% slower that way)
+            // of the table and a launch tail: R-MAT 20 builds in 104.5 ms so,
+            // in 108.0 with 2 throughout, 108.6 with 4, 108.7 with 4 first
+            // and 2 then, 135.9 with 8); after a small level, whose time is
+            // the latency of its trees, grow by 8, to have fewer levels
+            // (R-MAT 16: 5.63 ms, with 4 throughout 5.96, with 2 7.14; the
+            // labels of a root do not depend on the schedule, so neither
+            // does the schedule itself). The first pruned level of a directed
+            // build grows by 4: its combined graph's second level [16, 128)
+            // ends with a few large trees on small teams, and [16, 64) on
+            // teams of 5 builds the directed R-MAT 16 in 7.34 ms instead of
+            // 7.72 (the undirected one in 5.94 instead of 5.63)
             const int32_t f = g == 16 && B.partner ? 4
                               : level_labels >= LEVEL_LABELS_X2 ? (last_f == 2 ? 4 : 2)
                                                                 : 8;
@@ -998,7 +1005,9 @@ static int run_levels(Arena& A, Build& B, const chl_build_opts& o, void* scan_tm
             // build counts those of the partner h ^ 1, whose labels prune
             // h's tree), a cheap predictor of a large pruned tree (R-MAT 16,
             // level [128, 1024): rank correlation 0.45 with the tree's
-            // duration; builds 4.5% faster, the directed R-MAT 16 build 5%).
+            // duration). Worth 4.5% when an arc cost more; now R-MAT 20
+            // builds in 104.3 ms instead of 105.4, the directed R-MAT 16 in
+            // 7.40 instead of 7.45, R-MAT 16 in 5.63 instead of 5.57.
             // The order is computed and sorted on the stream, into B.roots.
             // (a group keeps rank order: roots close in rank reach the same
             // vertices)
@@ -1143,7 +1152,7 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
     HostCtl* hc = host_ctl();
     if (!hc) return CHL_ERR_HIP;
     // the pruned trees read the groups ordered by distance, as the other
-    // trees do; the groups in hub order serve the extensions and the cleaning
+    // trees do; the unsorted groups serve the extensions and the cleaning
     uint64_t* byd = nullptr;
     size_t byd_cap = 0;
     while (lo < n) {
@@ -1308,7 +1317,7 @@ static int chl_build_impl(const chl_graph* g, const int32_t* order, const chl_bu
     B.far2 = A.get<int32_t>(n);
     B.gstate = (int32_t*)A.get<int64_t>(plain_gstate_words() + 8);
     if (o.stats) B.stats = A.get<int64_t>((size_t)n * STAT_COLS);
-    // initial pool: 16 labels per vertex, grown on demand
+    // initial pool: 64 labels per vertex, grown on demand
     B.pool.cap = (unsigned long long)n * 64 + 4096;
     B.pool.v = A.get<int32_t>(B.pool.cap);
     B.pool.hub = A.get<int32_t>(B.pool.cap);

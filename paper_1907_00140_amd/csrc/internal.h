@@ -71,7 +71,7 @@ struct Slots {
     int64_t stride;       // elements per slot in key / touched / list arrays
     int64_t fstride;      // flag words per slot
     void* key;            // K[k][stride], all INF between trees
-    uint32_t* flags;      // [k][fstride], 4 bits per vertex, all 0 between trees
+    uint32_t* flags;      // [k][fstride], 4 bits per vertex (two used), all 0 between trees
     int32_t* touched;     // [k][stride]
     int32_t* lists;       // [k][3][stride]: two near lists, one far list
 };
@@ -173,13 +173,14 @@ int launch_directed_union(int32_t n, int64_t m, const int64_t* row, const int32_
                           int64_t* row2, int32_t* col2, int32_t* w2, int32_t* order2, hipStream_t st);
 int launch_directed_split(int32_t n, int64_t total, const int64_t* off2, int32_t* hub2, const int32_t* dist2,
                           int64_t* out_off, int32_t* out_hub, int32_t* out_dist, hipStream_t st);
-// out[64]: 16 samples x (row offset, ranking entry, neighbour, weight)
 // near[0] += sampled arcs whose ends' input ids differ by at most gap,
 // near[1] += arcs sampled (the caller has cleared both)
 int launch_sample_gaps(int32_t n, const int64_t* row_ptr, const int32_t* col, int32_t gap, int32_t* near,
                        hipStream_t st);
+// out[e] = arc e with the rank position of its target
 int launch_layout_arcs(int64_t m, const int32_t* col, const int32_t* w, const int32_t* pos, LayoutArc* out,
                        hipStream_t st);
+// out[64]: 16 samples x (row offset, ranking entry, neighbour, weight)
 int launch_sample_input(int32_t n, int64_t m, const int64_t* row_ptr, const int32_t* col, const int32_t* w,
                         const int32_t* order, int64_t* out, hipStream_t st);
 
@@ -190,12 +191,12 @@ int launch_scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, void* tem
 
 // segsort.hip: sort every segment [off[i], off[i+1]) of keys ascending; no
 // segment is longer than max_len
-size_t segsort_temp_bytes(int64_t nseg);
 int launch_segsort_u64(uint64_t* keys, const int64_t* off, int64_t nseg, int64_t total,
                        int64_t max_len, hipStream_t st);
 
 // tree.hip
-// phase: 0 main phase of a build, 1 autotuner probe, 2 common-label roots
+// phase: 0 main phase of a build, 1 autotuner probe, 2 pruning levels, 3
+// pruned construction of the Hybrid
 int launch_tree_batched(const TreeParams& p, int key_bits, int wg, int phase, hipStream_t st);
 int launch_tree_plain(const TreeParams& p, int key_bits, int wg, int grid, int32_t root,
                       int32_t* gstate, hipStream_t st);
@@ -209,6 +210,12 @@ constexpr int TEAM_WORDS = 32;
 int launch_tree_team(const TreeParams& p, int key_bits, int wg, int team_size, int nteams,
                      long long* tstate, int32_t* far2, hipStream_t st);
 int team_capacity(int key_bits, int wg);   // co-resident workgroups of the team kernel
+// Small trees: one 64-thread workgroup per tree, its state in LDS (at most
+// 128 vertices, at most 256 prefix labels of its root); roots of trees that
+// do not fit are appended to ovf (count *novf, zeroed by the caller) without
+// emitting anything. Same root queue, pool and statistics as the batched form.
+int launch_tree_small(const TreeParams& p, int key_bits, int nwg, int32_t* ovf, int32_t* novf, hipStream_t st);
+int small_capacity(int key_bits);   // co-resident workgroups of the small kernel
 // Groups: ngroups teams of team_size 1024-thread workgroups; each team grows
 // GROUP_TREES trees of consecutive queue entries at a time, their keys vertex-
 // major (group slot i: s.key holds n * GROUP_TREES keys at i * s.stride *
@@ -216,12 +223,6 @@ int team_capacity(int key_bits, int wg);   // co-resident workgroups of the team
 // i * 2n: two mask words per vertex, zero between groups; gstate GROUP_WORDS
 // words per team, zeroed before the launch). Cooperative launch; pbound <=
 // GROUP_MAX_PREFIX.
-// Small trees: one 64-thread workgroup per tree, its state in LDS (at most
-// 128 vertices, at most 256 prefix labels of its root); roots of trees that
-// do not fit are appended to ovf (count *novf, zeroed by the caller) without
-// emitting anything. Same root queue, pool and statistics as the batched form.
-int launch_tree_small(const TreeParams& p, int key_bits, int nwg, int32_t* ovf, int32_t* novf, hipStream_t st);
-int small_capacity(int key_bits);   // co-resident workgroups of the small kernel
 constexpr int GROUP_TREES = 16;
 constexpr int GROUP_WORDS = 256;
 constexpr int GROUP_MAX_PREFIX = 1024;
@@ -282,10 +283,10 @@ int launch_compact(const Pool& pool, uint64_t from, uint64_t cnt, const int32_t*
 // holds g2 - g words and off2 two. Everything stays on the stream.
 int launch_level_order(const int64_t* poff, int32_t g, int32_t g2, int32_t partner, uint64_t* keys,
                        int64_t* off2, int32_t* roots, hipStream_t st);
+// assemble.hip: sums[0..3] += settled, arcs, labels and rounds of cnt listed roots
+int launch_root_sums(int32_t cnt, const int32_t* roots, const int64_t* stats, int64_t* sums, hipStream_t st);
 // assemble.hip: totals of the per-root statistics (settled, arcs, stopped
 // early) into sums[0..2] (zeroed by the caller)
-// sums[0..3] += settled, arcs, labels and rounds of cnt listed roots
-int launch_root_sums(int32_t cnt, const int32_t* roots, const int64_t* stats, int64_t* sums, hipStream_t st);
 int launch_stat_sums(int32_t n, const int64_t* stats, int64_t* sums, hipStream_t st);
 constexpr int PRUNE_HEAD = 4;          // prefix labels of a vertex that are tested first (32 bytes)
 constexpr int HASH_MIN_PREFIX = 4096;   // prefixes from this size hash the root's distances
@@ -333,5 +334,23 @@ inline void clear_err(chl_labels* h) { *(volatile int32_t*)h->qerr = 0; }
 inline int32_t read_err(const chl_labels* h) { return *(volatile int32_t*)h->qerr; }   // after the stream's synchronisation
 #ifdef __HIPCC__
 __device__ __forceinline__ void set_invalid(int32_t* err) { *(volatile int32_t*)err = ERR_BIT_INVALID; }
+
+// LDS written by some lanes of a wave and read by others: order the wave's
+// accesses (a wave executes in lockstep; this keeps the compiler from moving
+// LDS accesses across the point)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Lower bound of hub x in hub[lo, hi).
+__device__ __forceinline__ int64_t lower_hub(const int32_t* __restrict__ hub, int64_t lo, int64_t hi, int32_t x) {
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (hub[mid] < x) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
 #endif
 }  // namespace chl

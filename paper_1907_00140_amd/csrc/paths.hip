@@ -76,23 +76,6 @@ struct ArcLds {
     int32_t w[64];
 };
 
-// LDS written by some lanes of a wave and read by others: order the wave's
-// accesses (a wave executes in lockstep; this keeps the compiler from moving
-// LDS accesses across the point)
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ int64_t lower_hub(const int32_t* __restrict__ hub, int64_t lo, int64_t hi, int32_t x) {
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (hub[mid] < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 struct ParentArgs {
     int32_t n;
     int64_t m;

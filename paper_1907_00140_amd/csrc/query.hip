@@ -15,15 +15,6 @@ namespace chl {
 
 namespace {
 
-// Lower bound of hub x in hub[lo, hi).
-__device__ __forceinline__ int64_t lower_hub(const int32_t* __restrict__ hub, int64_t lo, int64_t hi, int32_t x) {
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (hub[mid] < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 // Two tiers in one pass. Every lane first takes one query of its wave's 64:
 // when the shorter list has at most SMALL entries (a vertex with only its
 // own label, frequent in scale-free graphs, or very few), the lane answers
@@ -154,13 +145,7 @@ __global__ __launch_bounds__(256) void k_query_hash(int32_t n, const int64_t* __
     int32_t* hk = (int32_t*)lds4 + (threadIdx.x / GS) * 2 * T;   // hubs (-1: free), then distances
     int32_t* hd = hk + T;
     auto sync = [&]() {
-        if (NWV > 1) {
-            __syncthreads();
-        } else {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
+        if (NWV > 1) __syncthreads(); else wave_sync();
     };
     const int64_t ngrp = (int64_t)gridDim.x * GROUPS;
     int64_t k = (int64_t)blockIdx.x * GROUPS + threadIdx.x / GS;
@@ -286,11 +271,7 @@ __global__ __launch_bounds__(256) void k_query_group(int32_t n, const int64_t* _
             }
             for (int64_t i = ab + gl; i < ae; i += G) {
                 const int32_t x = ha[i];
-                int64_t lo = bb, hi = be;
-                while (lo < hi) {
-                    int64_t mid = (lo + hi) >> 1;
-                    if (hb[mid] < x) lo = mid + 1; else hi = mid;
-                }
+                const int64_t lo = lower_hub(hb, bb, be, x);
                 if (lo < be && hb[lo] == x) {
                     int64_t s = (int64_t)da[i] + (int64_t)db[lo];
                     best = s < best ? s : best;

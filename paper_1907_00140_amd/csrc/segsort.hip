@@ -213,8 +213,6 @@ int grid_cap(int64_t work) {
 
 }  // namespace
 
-size_t segsort_temp_bytes(int64_t) { return 0; }
-
 // A tier whose lengths no segment can have is not launched: it would only look
 // through the offsets. A label list is at most as long as there are hubs, so
 // the first levels take one tier (what it gives is measured with the scans').

@@ -22,8 +22,9 @@
 // clean vertex, the first vertex that is not final would be pending with its
 // final, clean key. The tree stops there; every clean key is then final.
 //
-// Dedup of the near lists uses 4 bits per vertex in a flag word array: bit 0/1
-// = "in near list 0/1" (the two near lists alternate between rounds). A vertex
+// Dedup of the near lists uses two of 4 bits per vertex in a flag word array:
+// bit 0/1 = "in near list 0/1" (the two near lists alternate between rounds;
+// the small-tree kernel has a bit for its far list too). A vertex
 // improved during a round is pushed to the next near list unless its bit for
 // that list is set, so every improvement made during a round is relaxed in the
 // next round, with no ordering needed between the key update and the flag
@@ -175,15 +176,6 @@ struct WaveQueue {
     uint32_t u[64 * (RELAX_ILP + 1)];
 };
 constexpr uint32_t MORE_BIT = 1u << 31;
-
-// LDS written by some lanes of a wave and read by others: order the wave's
-// accesses (a wave executes in lockstep; this keeps the compiler from moving
-// LDS accesses across the point)
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // What a relaxation needs besides the graph and the chunk. A vertex list is
 // a global array; the first lds entries of the next near list may live in
