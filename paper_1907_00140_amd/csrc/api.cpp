@@ -1070,12 +1070,13 @@ static int run_hybrid(Arena& A, Build& B, const chl_build_opts& o, const Slots& 
     // so it should be long; but the switch is seen at its end only, so it is
     // bounded by the graph, n/8 roots (and, under 1024, by what keeps the
     // workgroups busy twice over), not by the slots, of which there may be so
-    // many that one window holds half the graph. R-MAT 15 under a random
-    // ranking, threshold 100, crossed at root 18,547: windows up to 8 roots a
-    // slot switched at 32,256 (Psi 216), 141 ms; these at 19,968 (146), 137;
-    // n/16 throughout 142, n/32 at 18,944 (111) 152. R-MAT 16, crossed at
-    // 41,325: 48,128 (268), 704 ms; these 44,032 (153), 714; n/32 41,984 (121),
-    // 759.
+    // many that one window holds half the graph. Four R-MAT 15 graphs under a
+    // random ranking, threshold 100 (one crosses it at root 18,547): windows
+    // up to 8 roots a slot switched at 32,256 (Psi 324 to 606), builds of 134
+    // to 140 ms; these at 19,968 (107 to 146), 138 to 154 ms, 12 to 16 of them
+    // cleaning and regrouping: PLaNT trees for every root take 129. R-MAT 16,
+    // crossed at 41,325: 48,128 (268) 704 ms, these 44,032 (153) 713, windows
+    // of n/16 717, of n/32 41,984 (121) 759.
     const int64_t recent = std::max<int64_t>(64, n / 64);
     const int64_t wmax =
         std::max<int64_t>(recent, std::min<int64_t>(std::max<int64_t>(n / 8, 1024), 8 * (int64_t)s.k));
