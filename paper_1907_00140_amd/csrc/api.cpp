@@ -182,7 +182,8 @@ namespace {
 // ---------------------------------------------------------------- tuning
 // A setting that the caller fixed is part of the key: what was tuned around it
 // (four trees in flight, say, where a server caps them) is not what an
-// unrestricted build of the same graph would find.
+// unrestricted build of the same graph would find. (The Hybrid's threshold is
+// not: the trial trees are PLaNT trees whatever it is.)
 struct TuneKey {
     int32_t n;
     int64_t m;
